@@ -45,12 +45,25 @@ EDGE_CAP = 16384   # RAWALIGN_MAX_QUERY_LONG: longer queries keep one stripe up 
 def route_masks(b, single_max: int = 4096):
     """Pairs per kernel route, as the library's planner routes them: up to
     2048 levels, up to the single-stripe cut-off (single_max, and up to 4096
-    levels for queries too long for a stripe edge column), longer."""
+    levels for queries too long for a stripe edge column), longer.  single_max
+    0: the stripe sweep, timed as the long route, takes every region."""
     m = b.r_len.astype(np.int64)
     n = b.q_len.astype(np.int64)
+    if single_max == 0:
+        hi = (m > 2048) & (n > EDGE_CAP)
+        return {"lo": np.zeros(len(m), bool), "hi": hi, "long": ~hi}
     lo = m <= 2048
     hi = ~lo & ((m <= single_max) | ((m <= 4096) & (n > EDGE_CAP)))
     return {"lo": lo, "hi": hi, "long": ~lo & ~hi}
+
+
+def long_route(kw):
+    """(kernel, single_max of the route functions) of a call with these options."""
+    if kw.get("long_kernel", 0) == 1:
+        return "k_antidiag", kw.get("single_max") or 4096
+    if kw.get("mode", 1) == 0:
+        return "k_multi", kw.get("single_max") or 4096
+    return "k_sweep", 0
 
 
 def route_cells(b, single_max: int = 4096):
@@ -129,8 +142,8 @@ def cpu_baseline(b, seconds: float, gpu_score=None, gpu_end=None):
     return out
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_multi_uneven_batch_traffic.txt")
-KERNEL_SOURCES = ["dtw_device.h", "dtw_multi.hip", "internal.h"]
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_uneven_batch_traffic.txt")
+KERNEL_SOURCES = ["dtw_chain.h", "dtw_device.h", "dtw_rows.h", "dtw_sweep.hip", "internal.h"]
 
 
 def kernel_source_hash() -> str:
@@ -187,7 +200,7 @@ def valu_rate(iters: int = 20000):
     per CU, and the shader clock the cycle counter implies.  This is what
     the roofline's op peak (128 FP32 lane-operations per clock per CU, the
     datasheet's 157.3 TFLOP/s without the FMA credit) rests on; and the rate
-    of the constant clock behind the pipelined kernels' wait caps."""
+    of the constant clock behind the chained kernels' wait caps."""
     import ctypes
     import torch  # noqa: F401  (loads the HIP runtime first)
     path = os.path.join(ROOT, "paper_2310_05037_amd", "libvaluprobe.so")
@@ -208,7 +221,7 @@ def valu_rate(iters: int = 20000):
             row[f"{w}_waves_per_cu"] = {"lane_ops_per_clk_per_cu": rate.value, "clock_ghz": ghz.value,
                                         "kernel_ms": ms.value}
         out["forms"][name] = row
-    # Rate of the constant clock the pipelined kernels' capped waits count
+    # Rate of the constant clock the chained kernels' capped waits count
     # (s_memrealtime): ticks over one second of host wall time.
     L.clock_probe.argtypes = [ctypes.c_int, ctypes.POINTER(d), ctypes.POINTER(d)]
     ticks, secs = d(), d()
@@ -226,10 +239,9 @@ def serving_leg(n_reads: int, rate: float, streams: int = 3, slots: int = 3, cap
     30% of the reads off target (decoy candidates only: they never map and
     stream every chunk), the decision's match bonus set for this data's noise
     floor (workloads.SYNTHETIC_B_MATCH), resident rows in an 8 GiB arena,
-    three ticks in flight, each a captured graph in which the three route
-    kernels run on their own streams, regions above `single_max` levels
-    shared by `pipe_waves` waves each (the pipelined kernel; 0: one wave per
-    pair).  A short time-compressed run first warms up the graphs and
+    three ticks in flight, each a captured graph (`pipe_waves`, `single_max`
+    and `streams` change nothing in the
+    stripe sweep).  A short time-compressed run first warms up the graphs and
     caches.  The same reads then run again with an
     arena cap of `cap_frac` of the first run's peak: admission waits
     (back-pressure), the cap holds, and every read's per-chunk results must
@@ -646,8 +658,7 @@ def dominant_roofline(b, kt, valu_peak, long_name="k_multi", single_max: int = 4
             "ops_per_cell": VALU_OPS_PER_CELL}
 
 
-def batch_config_leg(lib, b, workload, valu_peak, tuned_extra, steps: int, warmup: int, antidiag: bool = False,
-                     pipeline: bool = False):
+def batch_config_leg(lib, b, workload, valu_peak, tuned_extra, steps: int, warmup: int, antidiag: bool = False):
     """One batch workload timed three or four ways on the same inputs: plain
     (static assignment, arrival order), persistent with the library
     defaults, persistent with the tuned settings, and (antidiag) the tuned
@@ -660,9 +671,6 @@ def batch_config_leg(lib, b, workload, valu_peak, tuned_extra, steps: int, warmu
         forms.append(("persistent_tuned_on_uneven_batch", tuned_extra))
     if antidiag:
         forms.append(("antidiag", dict(long_kernel=lib.LONG_ANTIDIAG)))
-    if pipeline:
-        for w in (2, 4, 8):
-            forms.append((f"pipeline_{w}_waves", dict(long_kernel=lib.LONG_PIPELINE, pipe_waves=w)))
     # the autotuner on this batch itself
     t0 = time.perf_counter()
     best = lib.rawalign_autotune(*db.args())
@@ -681,11 +689,8 @@ def batch_config_leg(lib, b, workload, valu_peak, tuned_extra, steps: int, warmu
         else:
             same = same and np.array_equal(res[0].view(np.uint32), ref[0].view(np.uint32)) and \
                 np.array_equal(res[1], ref[1])
-        kind = kw.get("long_kernel", 0)
         out[name] = {"value": b.cells / s / 1e9, "unit": "GCUPS", "ms_per_step": s * 1e3, "kernels_ms": kt,
-                     "roofline": dominant_roofline(b, kt, valu_peak,
-                                                   {1: "k_antidiag", 2: "k_pipe"}.get(kind, "k_multi"),
-                                                   kw.get("single_max") or 4096)}
+                     "roofline": dominant_roofline(b, kt, valu_peak, *long_route(kw))}
     out["all_forms_bit_identical"] = bool(same)
     del db
     torch.cuda.empty_cache()
@@ -767,8 +772,7 @@ def main():
         legs = {"plain_batch_4096": batch_config_leg(lib, workloads.plain_batch(), "plain_batch_4096_pairs",
                                                      valu_peak, {}, steps=10, warmup=2),
                 "long_stress_1024": batch_config_leg(lib, workloads.long_stress(), "long_stress_1024_x_10000_x_20000",
-                                                     valu_peak, {}, steps=args.steps, warmup=1, antidiag=True,
-                                                     pipeline=True)}
+                                                     valu_peak, {}, steps=args.steps, warmup=1, antidiag=True)}
         print(json.dumps({"configs": legs}), flush=True)
         return
     if args.only_banded:
@@ -798,9 +802,8 @@ def main():
     extra_other = dict(extra)
     if int(extra_other.get("long_kernel", 0)) == lib.LONG_ANTIDIAG:
         extra_other.update(long_kernel=lib.LONG_STRIPED, long_waves_per_cu=0)
-    single_max = int(extra.get("single_max") or 4096)
+    long_name, single_max = long_route(extra)
     rc = route_cells(b, single_max)
-    long_name = {1: "k_antidiag", 2: "k_pipe"}.get(int(extra.get("long_kernel", 0)), "k_multi")
     plain_opts = lib.make_opts(mode=lib.MODE_PLAIN, flags=lib.FLAG_TIMING)
 
     def timed(opts, steps, warmup):
@@ -831,16 +834,6 @@ def main():
                                      "kernels_ms": akt,
                                      "long_route_gcups": route_cells(b)["long"] / akt["long_ms"] / 1e6,
                                      "kernel": "k_antidiag"}
-        # Same batch with the regions above one stripe shared by 4 waves each
-        # (pipelined stripes), at the tuned cut-off.
-        pp_opts = lib.make_opts(flags=lib.FLAG_TIMING, long_kernel=lib.LONG_PIPELINE, pipe_waves=4,
-                                single_max=single_max)
-        note("pipeline variant")
-        pp_s, pkt4 = timed(pp_opts, 3, 1)
-        variants["long_pipeline_4_waves"] = {"value": cells / pp_s / 1e9, "unit": "GCUPS",
-                                             "ms_per_step": pp_s * 1e3, "kernels_ms": pkt4,
-                                             "long_route_gcups": rc["long"] / pkt4["long_ms"] / 1e6,
-                                             "kernel": "k_pipe", "single_max": single_max}
 
     if not args.skip_plain:
         note("early termination")
@@ -873,7 +866,7 @@ def main():
         note("long stress")
         configs["long_stress_1024"] = batch_config_leg(lib, workloads.long_stress(),
                                                       "long_stress_1024_x_10000_x_20000", valu_peak, extra,
-                                                      steps=3, warmup=1, antidiag=True, pipeline=True)
+                                                      steps=3, warmup=1, antidiag=True)
         for name, leg in configs.items():
             checks[f"{name}_forms_bit_identical"] = leg["all_forms_bit_identical"]
 

@@ -67,16 +67,15 @@ extern "C" {
 
 /* Scheduling modes of rawalign_dtw_batch_ex. */
 #define RAWALIGN_MODE_PLAIN 0       /* one workgroup per pair in arrival order, fixed grids */
-#define RAWALIGN_MODE_PERSISTENT 1  /* device-sized grids, atomic work queues, longest pairs first */
+#define RAWALIGN_MODE_PERSISTENT 1  /* device-sized grids, atomic work queues, longest pairs first, long pairs cut
+                                       into stripes that several waves sweep at once (the stripe sweep) */
 
 /* Kernels for regions longer than one stripe (above opts.single_max levels). */
-#define RAWALIGN_LONG_STRIPED 0     /* one wave sweeps the stripes in turn, edges through device memory */
+#define RAWALIGN_LONG_STRIPED 0     /* the stripe sweep (plain mode: one wave sweeps a pair's stripes in turn) */
 #define RAWALIGN_LONG_ANTIDIAG 1    /* one 256-thread workgroup per pair sweeps anti-diagonals of R x 8 tiles,
                                        edges through LDS (Sec. 2.4.4);
                                        plain batches only (rawalign_dtw_extend rejects it) */
-#define RAWALIGN_LONG_PIPELINE 2    /* opts.pipe_waves waves share each pair, one stripe each in turn, the
-                                       stripes pipelined: a stripe starts as soon as its left neighbour has
-                                       stored the edge rows it needs (waits on LDS counters, no barriers) */
+#define RAWALIGN_LONG_PIPELINE 2    /* as RAWALIGN_LONG_STRIPED: waves share a pair's stripes there by themselves */
 
 /* opts.flags */
 #define RAWALIGN_FLAG_TIMING 1      /* record hipEvents around every kernel (rawalign_last_timing) */
@@ -87,18 +86,18 @@ extern "C" {
 typedef struct rawalign_opts {
     int32_t mode;               /* RAWALIGN_MODE_* */
     int32_t long_kernel;        /* RAWALIGN_LONG_* */
-    int32_t lo_waves_per_cu;    /* persistent grid of the <= 2048-level kernel, per CU (0 = occupancy limit) */
+    int32_t lo_waves_per_cu;    /* persistent grid of the <= 2048-level kernel, per CU (0 = occupancy limit); the
+                                   stripe sweep takes the largest of the three, occupancy if one is 0 */
     int32_t hi_waves_per_cu;    /* same, 2049..4096 levels */
     int32_t long_waves_per_cu;  /* same, > 4096 levels (anti-diagonal kernel: workgroups per CU, 0 = occupancy, 5) */
-    int32_t streams;            /* 1: the three kernels run one after another on `stream`;
-                                   3: concurrently on internal streams joined back to `stream` */
+    int32_t streams;            /* 1: the kernels run one after another on `stream`;
+                                   3: concurrently on internal streams joined back to `stream` (without effect on
+                                   the stripe sweep, which is one kernel) */
     int32_t flags;              /* RAWALIGN_FLAG_* */
-    int32_t single_max;         /* widest region (levels) swept as one stripe: 2048 or 4096 (0 = 4096).  Regions
-                                   of 2049..4096 levels then take one stripe of 34..64 columns per lane (two
-                                   waves per SIMD) or two stripes of 17..32 (four waves per SIMD); a query longer
-                                   than RAWALIGN_MAX_QUERY_LONG keeps one stripe either way */
-    int32_t pipe_waves;         /* RAWALIGN_LONG_PIPELINE: waves per workgroup sharing a pair, 2, 4 or 8 (0 = 4);
-                                   long_waves_per_cu then counts waves of that kernel per CU */
+    int32_t single_max;         /* anti-diagonal kernel and plain mode: widest region (levels) swept as one stripe,
+                                   2048 or 4096 (0 = 4096); a query longer than RAWALIGN_MAX_QUERY_LONG keeps one
+                                   stripe up to 4096 levels either way */
+    int32_t pipe_waves;         /* RAWALIGN_LONG_PIPELINE: 2, 4, 8 or 0; without effect */
 } rawalign_opts;
 
 /* Fill `opts` with the library defaults (persistent mode, striped long
@@ -120,12 +119,17 @@ int rawalign_opts_default(rawalign_opts *opts);
  *   out_end       device, int32 per pair: 0-based index j into the pair's
  *                 region where the best path ends (smallest on ties)
  *
- * Internal scratch (planning lists, queue counters) is allocated by the
- * library per (device, stream) on first use, grown when a larger batch
+ * Internal scratch (planning lists, queue counters, and for persistent calls
+ * the stripe sweep's work items and edge columns, up to 0.9 GB) is allocated
+ * by the library per (device, stream) on first use, grown when a larger batch
  * arrives and kept until process exit.  Calls on one stream are ordered by
  * the stream; calls on different streams use different scratch.  Growing the
  * scratch calls hipMalloc, so a call that may be captured into a HIP graph
- * must follow an uncaptured call of at least the same n_pairs on that stream.
+ * must follow an uncaptured call of at least the same n_pairs on that stream;
+ * captured before the sweep's own scratch is there, a call takes the kernels
+ * of plain mode's routes in persistent queues instead.  A sweep whose waves
+ * wait for each other longer than 5 s (a GPU that does not run them) ends with
+ * NaN and end -5 for the pairs it cut.
  */
 int rawalign_dtw_batch(const float *q, int64_t q_size, const int64_t *q_off, const int32_t *q_len,
                        const float *r, int64_t r_size, const int64_t *r_off, const int32_t *r_len,
@@ -423,14 +427,11 @@ int rawalign_chain_decide(const float *gap_cost, int64_t n_gaps, const int64_t *
  * out_end are scratch outputs) and keeps the fastest as this device's tuned
  * setting, which opts == NULL then selects.  Two stages, each candidate one
  * warm-up call and the mean of three:
- *   1. the kernel shape: the single-stripe cut-off (single_max 4096 or 2048,
- *      i.e. 34..64 columns per lane on one stripe or 17..32 on two for
- *      regions of 2049..4096 levels) times the long-route kernel and its
- *      workgroup shape (one wave per pair, 2, 4 or 8 waves sharing each
- *      pair: RAWALIGN_LONG_PIPELINE, or one 256-thread workgroup per pair:
- *      RAWALIGN_LONG_ANTIDIAG);
- *   2. at that shape: one or three streams, and each route's persistent grid
- *      at or below its occupancy limit.
+ *   1. the kernel shape: the stripe sweep, or the anti-diagonal kernel
+ *      (RAWALIGN_LONG_ANTIDIAG) for regions above a single-stripe cut-off of
+ *      4096 or 2048 levels;
+ *   2. at that shape: the persistent grids at or below occupancy, and one or
+ *      three streams beside the anti-diagonal kernel.
  * Every candidate returns the same bits, so the choice affects time only.
  * The anti-diagonal kernel serves plain batches only: calls of the other
  * entry points that inherit a tuned setting naming it (opts NULL) take the

@@ -12,8 +12,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librawalign.so")
 
-SOURCES = ["dtw_single.hip", "dtw_multi.hip", "dtw_antidiag.hip", "dtw_plan.hip", "dtw_bnb.hip", "dtw_global.hip",
-           "dtw_band.hip", "dtw_path.hip", "dtw_noalloc.hip", "dtw_pipe.hip",
+SOURCES = ["dtw_sweep.hip", "dtw_single.hip", "dtw_multi.hip", "dtw_antidiag.hip", "dtw_plan.hip", "dtw_bnb.hip", "dtw_global.hip",
+           "dtw_band.hip", "dtw_path.hip", "dtw_noalloc.hip",
            "rawalign_abi.cpp"]
 
 HIPCC_FLAGS = [

@@ -221,7 +221,8 @@ RA_DEV void load_lane(const PairView &pv, int col0, float (&rv)[C], float (&A)[C
     const __amdgpu_buffer_rsrc_t rrs = make_rsrc(pv.r, pv.m);
     __amdgpu_buffer_rsrc_t wrs = rrs;
     if (EXT) wrs = make_rsrc(pv.row, pv.m);
-    const float row0 = pv.corner ? kInf : 0.0f;
+    float row0 = pv.corner ? kInf : 0.0f;
+    asm volatile("" : "+v"(row0));   // set here, not as C registers kept across pairs
 #pragma unroll
     for (int s = 0; s < C; ++s) {
         const int jc = col0 + (s < last ? s : last);   // clamped into the region
@@ -245,15 +246,10 @@ RA_DEV void finish_lane(const PairView &pv, int col0, const float (&A)[C], float
     const int lim = pv.m - col0;
     best = kInf;
     bj = 0x7fffffff;
-    if (!EXT && pv.fixed_end) {
-#pragma unroll
-        for (int s = 0; s < C; ++s)
-            if (s == lim - 1) take_min(best, bj, A[s], col0 + s);
-        return;
-    }
+    const int first = !EXT && pv.fixed_end ? lim - 1 : 0;
 #pragma unroll
     for (int s = 0; s < C; ++s) {
-        if (s < lim) {
+        if (s < lim && s >= first) {
             take_min(best, bj, A[s], col0 + s);
             if (EXT) pv.row[col0 + s] = A[s];
         }
@@ -303,26 +299,6 @@ RA_DEV void two_steps2(int t, int n, int lane, const float (&rv)[C], float (&A)[
     if (EOUT && t >= 126 && t - 126 < n && lane == 63) edge[t - 126] = A[C - 1];
 }
 
-// Cross-wave hand-over hook of the sweep (the multi-wave pipeline,
-// dtw_pipe.hip).  NoSync, the default, is compiled out entirely.  An active
-// policy is called every kBlock steps of the sweep:
-//   wait(rows):     before the edge values of rows < rows are loaded (the
-//                   stripe to the left must have stored them); false after a
-//                   time-out, and the sweep then runs on without waiting;
-//   publish(rows):  after this stripe's lane 63 has stored the edge values of
-//                   rows < rows;
-//   set_corner(v):  this stripe's row -1 value in its last column, handed
-//                   to the next stripe before any row is published;
-//   corner():       the corner left of this stripe, read after the first wait.
-struct NoSync {
-    static constexpr bool kActive = false;
-    static constexpr int kBlock = 64;
-    RA_DEV bool wait(int) { return true; }
-    RA_DEV void publish(int) {}
-    RA_DEV void set_corner(float) {}
-    RA_DEV float corner() { return 0.0f; }
-};
-
 // One column stripe [col_base, col_base + 64*C) of a pair on one wave.
 // Returns this stripe's (min, argmin) of row n-1 over columns < m.  ILP2:
 // two independent chains per lane and step (lane skew 2, see row_step2),
@@ -331,18 +307,14 @@ struct NoSync {
 //   next_corner: receives D(-1, col_base+64C-1) for the next stripe.  Both
 //                travel in registers because the resident row is updated in
 //                place, stripe by stripe.
-template <int C, bool EXT, bool EIN, bool EOUT, bool ILP2, class SYNC = NoSync>
+template <int C, bool EXT, bool EIN, bool EOUT, bool ILP2>
 RA_DEV void sweep(const PairView &pv, int col_base, float *edge, float corner, float &next_corner, float &best,
-                  int &bj, SYNC *sync = nullptr) {
-    static_assert(!SYNC::kActive || !ILP2, "the hand-over assumes a skew of one lane per step");
+                  int &bj) {
     const int lane = opaque_lane();
     const int col0 = col_base + lane * C;
     float rv[C], A[C], B[C];
     load_lane<C, EXT>(pv, col0, rv, A, B);
     next_corner = __shfl(A[C - 1], 63, 64);
-    if constexpr (SYNC::kActive) {
-        if (EOUT) sync->set_corner(next_corner);
-    }
     const int n = pv.n;
     if (n > 0) {
         // Left boundary of the region: D(i,-1) = +inf for every row.  At row
@@ -364,36 +336,12 @@ RA_DEV void sweep(const PairView &pv, int col_base, float *edge, float corner, f
         float qa = uload(qrs, 0, nm1, qrev), qb = uload(qrs, 1, nm1, qrev);
         float ea = 0.0f, eb = 0.0f;
         if (EIN) {
-            if constexpr (SYNC::kActive) {
-                // rows [0, kBlock + 2) before the first loads; the corner
-                // was handed over before any row was published
-                (void)sync->wait(n < SYNC::kBlock + 2 ? n : SYNC::kBlock + 2);
-                E1 = sync->corner();
-            }
             ea = uload(ers, 0, nm1);
             eb = uload(ers, 1, nm1);
         }
         int t = 0;
-        // Every kBlock steps: wait for the edge rows the next kBlock steps
-        // load (up to t + kBlock + 1) and publish the rows lane 63 has
-        // stored (it stores row u - 63 at step u, so steps 0 .. t-1 stored
-        // rows 0 .. t-64).
-#define RA_SYNC_POINT                                                                        \
-    if constexpr (SYNC::kActive) {                                                           \
-        if ((t & (SYNC::kBlock - 1)) == 0) {                                                 \
-            if (EIN) {                                                                       \
-                const int need = t + SYNC::kBlock + 2;                                       \
-                (void)sync->wait(need < n ? need : n);                                       \
-            }                                                                                \
-            if (EOUT) {                                                                      \
-                const int done = t - 63;                                                     \
-                sync->publish(done < 0 ? 0 : (done < n ? done : n));                         \
-            }                                                                                \
-        }                                                                                    \
-    }
 #define RA_STEPS(MASKED)                                                                     \
     {                                                                                        \
-        RA_SYNC_POINT                                                                        \
         const float q0 = qa, q1 = qb, e0 = ea, e1 = eb;                                      \
         qa = uload(qrs, t + 2, nm1, qrev);                                                   \
         qb = uload(qrs, t + 3, nm1, qrev);                                                   \
@@ -410,13 +358,34 @@ RA_DEV void sweep(const PairView &pv, int col_base, float *edge, float corner, f
         for (; t < tb; t += 2) RA_STEPS(false)
         for (; t < T; t += 2) RA_STEPS(true)
 #undef RA_STEPS
-#undef RA_SYNC_POINT
-        if constexpr (SYNC::kActive) {
-            if (EOUT) sync->publish(n);   // every edge row is stored
-        }
     }
     finish_lane<C, EXT>(pv, col0, A, best, bj);
     wave_min(best, bj);
+}
+
+// Work items of a pair in the stripe sweep: each sweeps k stripes of 64 c
+// columns one after another.  lim = 0: one item.  Else lim is what one item
+// may cost, in cells per lane (a share of the batch's cells per resident
+// wave): a longer one would end after the rest of the batch, so the pair is
+// cut into items of one stripe that run beside each other (an item of several
+// would hold up its right neighbour until its last).  Items narrower than 64
+// sqrt(26 m / n) columns, or 64 kSweepMinC, do not pay: each starts about 166
+// rows after its left neighbour, and a row of c columns costs a lone wave about
+// 52 + 5.2 c ns, so (n + 166 m / (64 c)) (52 + 5.2 c) is least there.
+RA_DEV void sweep_shape(int n, int m, float lim, int &items, int &k, int &c) {
+    const int stripes = m > kSweepStripe ? (m + kSweepStripe - 1) / kSweepStripe : 1;
+    items = 1;
+    if (lim > 0.0f) {
+        const float rows = (float)(n < 1 ? 1 : n), cols = (float)m;
+        const float want = ceilf(rows * cols / (64.0f * lim));
+        const float most = ceilf(cols / (64.0f * fmaxf((float)kSweepMinC, sqrtf(26.0f * cols / rows))));
+        const int more = (int)fminf(want, most);
+        if (want > 1.0f) items = more > stripes ? more : stripes;
+    }
+    k = items > 1 ? 1 : stripes;
+    c = (m + 64 * items * k - 1) / (64 * items * k);
+    if (c < 1) c = 1;
+    if (items > 1) items = (m + 64 * c - 1) / (64 * c);   // every item starts inside the region
 }
 
 // Stripe shape of a region of m levels: S stripes of 64*C columns,

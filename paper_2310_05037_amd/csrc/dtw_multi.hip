@@ -1,4 +1,5 @@
-// dtw_multi.hip -- regions longer than 4096 levels: one wave sweeps S column
+// dtw_multi.hip -- regions longer than 4096 levels where a wave takes whole
+// pairs (plain batches, gaps between anchors, the allocation-free call): it sweeps S column
 // stripes of at most 256 kMultiMaxK columns (2048 by default) one after
 // another.  Lane 63 writes each stripe's last column to the wave's own edge
 // slot in device memory; the next stripe's lane 0 reads it back as its left
@@ -31,6 +32,7 @@ void k_multi(PairArrays a, const int32_t *__restrict__ list, const int32_t *__re
              int32_t *queue, float *edge_base) {
     float *edge = edge_base + (size_t)blockIdx.x * kEdgeCap;
     const int n_items = *count;
+    if (n_items == 0) return;
     int item = blockIdx.x;
     if (queue) {
         int it = 0;

@@ -10,7 +10,10 @@ struct PlanArgs {
     int buckets;      // 1: single bucket (plain), kBuckets: LPT buckets
     int extend;
     int single_max;   // widest region of the single-stripe routes
+    int chain;        // the sweep's pairs are listed stripe by stripe (sw)
+    float lim_scale;  // share of the batch's cells that one item may have, per lane
     PlanScratch s;
+    SweepScratch sw;
     const int32_t *band;   // banded planning (band half-width per pair), else null
 };
 
@@ -113,7 +116,8 @@ RA_DEV int classify(const PlanArgs &pa, int64_t p, int &bucket, float &score, in
     // single stripe whose query is too long for a stripe edge column keep
     // one stripe whatever the cut-off, so the result never depends on it.
     int route;
-    if (m <= kSingleLoMaxRegion) route = kRouteSingleLo;
+    if (pa.chain) route = m > kSweepStripe && n > kEdgeCap ? kRouteSingleHi : kRouteSingleLo;
+    else if (m <= kSingleLoMaxRegion) route = kRouteSingleLo;
     else if (m <= pa.single_max || (m <= kSingleMaxRegion && n > kEdgeCap)) route = kRouteSingleHi;
     else route = kRouteMulti;
     bucket = 0;
@@ -131,24 +135,11 @@ RA_DEV int classify(const PlanArgs &pa, int64_t p, int &bucket, float &score, in
     return route;
 }
 
-__global__ void k_plan_zero(PlanScratch s) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kNumRoutes * kBuckets) s.hist[i] = 0;
-    if (i < kNumRoutes) {
-        s.counts[i] = 0;
-        s.queue[i] = 0;
-    }
-}
-
 // 1024 threads: each thread classifies a few pairs of a million-pair batch,
 // one after another; at 256 threads that chain of dependent loads set the
 // planning time.
 constexpr int kPlanBlock = 1024;
 constexpr int kBins = kNumRoutes * kBuckets;
-// Workgroups take contiguous ranges of pairs; at most kPlanGrid of them, so
-// a batch of millions of pairs still adds each busy bin to the global
-// histogram only a few hundred times.
-constexpr int kPlanGrid = 512;
 
 RA_DEV void plan_range(int64_t n_pairs, int64_t &lo, int64_t &hi) {
     const int64_t per = ((n_pairs + gridDim.x - 1) / gridDim.x + kPlanBlock - 1) / kPlanBlock * kPlanBlock;
@@ -156,45 +147,156 @@ RA_DEV void plan_range(int64_t n_pairs, int64_t &lo, int64_t &hi) {
     hi = lo + per < n_pairs ? lo + per : n_pairs;
 }
 
-// Each workgroup counts its pairs per (route, bucket) in LDS and adds the
-// non-zero bins to the global histogram: one global atomic per bin per
-// workgroup instead of one per pair.  Pairs that need no kernel get their
-// result here.
-__global__ __launch_bounds__(kPlanBlock) void k_plan_count(PlanArgs pa) {
-    __shared__ int h[kBins];
-    for (int i = threadIdx.x; i < kBins; i += kPlanBlock) h[i] = 0;
+// Sum over the workgroup, for every thread.
+RA_DEV double block_sum(double v) {
+    __shared__ double part[kPlanBlock / 64];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
     __syncthreads();
-    int64_t lo, hi;
-    plan_range(pa.n_pairs, lo, hi);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int i = 0; i < kPlanBlock / 64; ++i) t += part[i];
+    return t;
+}
+
+// What a pair takes of its route's list: one entry, or its work items.
+RA_DEV int list_slots(const PlanArgs &pa, int64_t p, int route, float lim, int &k, int &c) {
+    if (!pa.chain || route != kRouteSingleLo) return 1;
+    int items;
+    sweep_shape(pa.a.q_len[p], pa.a.r_len[p], lim, items, k, c);
+    return items;
+}
+
+RA_DEV void write_slots(const PlanArgs &pa, int64_t p, int route, int slots, int k, int c, int at) {
+    if (!pa.chain || route != kRouteSingleLo) {
+        pa.s.list[route * pa.s.capacity + at] = (int32_t)p;
+        return;
+    }
+    for (int i = 0; i < slots; ++i)
+        if (at + i < pa.sw.item_cap) pa.sw.items[at + i] = pack_item({(int)p, c, k, i, slots});
+}
+
+// Phase 0 of a planning workgroup: cells of the pairs [lo, hi).
+RA_DEV double plan_cells(const PlanArgs &pa, int64_t lo, int64_t hi) {
+    double cells = 0.0;
+    if (pa.chain) {
+        for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock)
+            if (slices_ok(pa.a, p, pa.extend != 0)) cells += (double)pa.a.q_len[p] * (double)pa.a.r_len[p];
+    }
+    return block_sum(cells);
+}
+
+// Clears the sweep's slot counters and, after a call with a wait that timed
+// out, refills its ring; every thread of the grid takes part.
+RA_DEV void reset_ring(const PlanArgs &pa) {
+    const int64_t i0 = (int64_t)blockIdx.x * kPlanBlock + threadIdx.x;
+    const int64_t step = (int64_t)gridDim.x * kPlanBlock;
+    for (int64_t i = i0; i < pa.sw.ring_slots; i += step) pa.sw.done[i] = 0;
+    if (*pa.sw.failed) {
+        const int64_t words = (int64_t)pa.sw.ring_slots * kSlotFloats;
+        for (int64_t i = i0; i < words; i += step) reinterpret_cast<uint32_t *>(pa.sw.ring)[i] = 0xffffffffu;
+    }
+}
+
+// Counts the pairs [lo, hi) per (route, bucket) into h; pairs that need no
+// kernel get their result here.
+RA_DEV void plan_count(const PlanArgs &pa, int64_t lo, int64_t hi, float lim, int *h) {
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
-        int b = 0, e = 0;
+        int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
         const int route = classify(pa, p, b, sc, e);
         if (route >= 0) {
-            atomicAdd(&h[route * kBuckets + b], 1);
+            atomicAdd(&h[route * kBuckets + b], list_slots(pa, p, route, lim, k, c));
         } else if (route == -1) {
             pa.a.out_score[p] = sc;
             if (pa.a.out_end) pa.a.out_end[p] = e;
         }
     }
+}
+
+// Writes the pairs [lo, hi) to their lists; next[bin] is the bin's cursor.
+RA_DEV void plan_scatter(const PlanArgs &pa, int64_t lo, int64_t hi, float lim, const int *base, int *next) {
+    for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
+        int b = 0, e = 0, k = 0, c = 0;
+        float sc = 0.0f;
+        const int route = classify(pa, p, b, sc, e);
+        if (route >= 0) {
+            const int bin = route * kBuckets + b;
+            const int slots = list_slots(pa, p, route, lim, k, c);
+            write_slots(pa, p, route, slots, k, c, (base ? base[bin] : 0) + atomicAdd(&next[bin], slots));
+        }
+    }
+}
+
+// Exclusive scan of each route's bins (bucket 0 first), one wave per route:
+// three buckets per lane.
+RA_DEV void plan_scan(const PlanArgs &pa, int *hist) {
+    static_assert(kBuckets == 3 * 64, "three buckets per lane");
+    const int route = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (route >= kNumRoutes) return;
+    int *h = hist + route * kBuckets + 3 * lane;
+    const int a0 = h[0], a1 = h[1], a2 = h[2];
+    int run = a0 + a1 + a2;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int x = __shfl_up(run, off, 64);
+        if (lane >= off) run += x;
+    }
+    const int excl = run - (a0 + a1 + a2);
+    h[0] = excl;
+    h[1] = excl + a0;
+    h[2] = excl + a0 + a1;
+    if (lane == 63) {
+        pa.s.counts[route] = run;
+        pa.s.queue[route] = 0;
+        if (pa.chain && route == kRouteSingleLo) {
+            *pa.sw.n_items = run < pa.sw.item_cap ? run : (int)pa.sw.item_cap;
+            for (int x = 0; x < kQueues; ++x) pa.sw.queue[x * kQueueStride] = 0;
+            *pa.sw.failed = 0;
+        }
+    }
+}
+
+// Clears the histogram; chained sweep: cells of each workgroup's range.
+__global__ __launch_bounds__(kPlanBlock) void k_plan_start(PlanArgs pa) {
+    const int i = blockIdx.x * kPlanBlock + threadIdx.x;
+    if (i < kBins) pa.s.hist[i] = 0;
+    if (!pa.chain) return;
+    reset_ring(pa);
+    int64_t lo, hi;
+    plan_range(pa.n_pairs, lo, hi);
+    const double cells = plan_cells(pa, lo, hi);
+    if (threadIdx.x == 0) pa.sw.partial[blockIdx.x] = cells;
+}
+
+// Total cells of the batch -> what one item may cost (see sweep_shape).
+RA_DEV float plan_lim(const PlanArgs &pa, double cells) {
+    const float lim = (float)cells * pa.lim_scale;
+    return pa.chain ? fmaxf(lim, 1.0f) : 0.0f;
+}
+RA_DEV float plan_lim_of_grid(const PlanArgs &pa) {
+    if (!pa.chain) return 0.0f;
+    return plan_lim(pa, block_sum(threadIdx.x < gridDim.x ? pa.sw.partial[threadIdx.x] : 0.0));
+}
+
+// Each workgroup counts its pairs per (route, bucket) in LDS and adds the
+// non-zero bins to the global histogram: one global atomic per bin per
+// workgroup instead of one per pair.
+__global__ __launch_bounds__(kPlanBlock) void k_plan_count(PlanArgs pa) {
+    __shared__ int h[kBins];
+    for (int i = threadIdx.x; i < kBins; i += kPlanBlock) h[i] = 0;
+    const float lim = plan_lim_of_grid(pa);
+    __syncthreads();
+    int64_t lo, hi;
+    plan_range(pa.n_pairs, lo, hi);
+    plan_count(pa, lo, hi, lim, h);
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += kPlanBlock)
         if (h[i]) atomicAdd(&pa.s.hist[i], h[i]);
 }
 
-// Exclusive scan of each route's histogram (bucket 0 first) -> cursors.
-__global__ void k_plan_scan(PlanScratch s) {
-    const int route = threadIdx.x;
-    if (route >= kNumRoutes) return;
-    int run = 0;
-    for (int b = 0; b < kBuckets; ++b) {
-        const int c = s.hist[route * kBuckets + b];
-        s.hist[route * kBuckets + b] = run;
-        run += c;
-    }
-    s.counts[route] = run;
-    s.queue[route] = 0;
-}
+__global__ __launch_bounds__(64 * kNumRoutes) void k_plan_scan(PlanArgs pa) { plan_scan(pa, pa.s.hist); }
 
 // Each workgroup counts its range per bin in LDS, reserves one contiguous
 // range per bin with a single global atomic on the bin's cursor, then ranks
@@ -205,14 +307,15 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_scatter(PlanArgs pa) {
     __shared__ int cnt[kBins];
     __shared__ int base[kBins];
     for (int i = threadIdx.x; i < kBins; i += kPlanBlock) cnt[i] = 0;
+    const float lim = plan_lim_of_grid(pa);
     __syncthreads();
     int64_t lo, hi;
     plan_range(pa.n_pairs, lo, hi);
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
-        int b = 0, e = 0;
+        int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
         const int route = classify(pa, p, b, sc, e);
-        if (route >= 0) atomicAdd(&cnt[route * kBuckets + b], 1);
+        if (route >= 0) atomicAdd(&cnt[route * kBuckets + b], list_slots(pa, p, route, lim, k, c));
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += kPlanBlock) {
@@ -220,50 +323,73 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_scatter(PlanArgs pa) {
         cnt[i] = 0;
     }
     __syncthreads();
-    for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
-        int b = 0, e = 0;
-        float sc = 0.0f;
-        const int route = classify(pa, p, b, sc, e);
-        if (route >= 0) {
-            const int bin = route * kBuckets + b;
-            pa.s.list[route * pa.s.capacity + base[bin] + atomicAdd(&cnt[bin], 1)] = (int32_t)p;
-        }
+    plan_scatter(pa, lo, hi, lim, base, cnt);
+}
+
+// Small batches: the same phases in one workgroup, one launch instead of
+// four (a launch between dependent kernels costs more than planning a few
+// thousand pairs).
+constexpr int64_t kPlanSmall = 4096;
+__global__ __launch_bounds__(kPlanBlock) void k_plan_small(PlanArgs pa) {
+    __shared__ int h[kBins];
+    for (int i = threadIdx.x; i < kBins; i += kPlanBlock) h[i] = 0;
+    float lim = 0.0f;
+    if (pa.chain) {
+        reset_ring(pa);
+        lim = plan_lim(pa, plan_cells(pa, 0, pa.n_pairs));
     }
+    __syncthreads();
+    plan_count(pa, 0, pa.n_pairs, lim, h);
+    __syncthreads();
+    plan_scan(pa, h);
+    __syncthreads();
+    plan_scatter(pa, 0, pa.n_pairs, lim, nullptr, h);
 }
 
 static hipError_t run_plan(const PlanArgs &pa, hipStream_t stream) {
-    const PlanScratch &s = pa.s;
     const int64_t n_pairs = pa.n_pairs;
-    hipLaunchKernelGGL(k_plan_zero, dim3((kBins + 255) / 256), dim3(256), 0, stream, s);
+    if (n_pairs <= kPlanSmall) {
+        hipLaunchKernelGGL(k_plan_small, dim3(1), dim3(kPlanBlock), 0, stream, pa);
+        return hipGetLastError();
+    }
     const int64_t g64 = (n_pairs + kPlanBlock - 1) / kPlanBlock;
     const unsigned g = (unsigned)(g64 < kPlanGrid ? g64 : kPlanGrid);
+    static_assert(kPlanGrid <= kPlanBlock && kBins <= kPlanBlock * (kPlanSmall / kPlanBlock), "start kernel covers both");
+    hipLaunchKernelGGL(k_plan_start, dim3(g), dim3(kPlanBlock), 0, stream, pa);
     hipLaunchKernelGGL(k_plan_count, dim3(g), dim3(kPlanBlock), 0, stream, pa);
-    hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(64), 0, stream, s);
+    hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(64 * kNumRoutes), 0, stream, pa);
     hipLaunchKernelGGL(k_plan_scatter, dim3(g), dim3(kPlanBlock), 0, stream, pa);
     return hipGetLastError();
 }
 
+// One item's share of the batch, in what every resident wave would get.  On
+// the 4,096-pair batch 0.91 ms (1.08 at half the share, 0.97 at twice), the
+// 10,000-pair uneven batch with starts 10.7 ms (11.8, 12.4).
+constexpr float kItemShare = 1.0f;
+
 hipError_t launch_plan(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg, const PlanScratch &s,
-                       hipStream_t stream) {
-    PlanArgs pa;
+                       const SweepScratch *sw, hipStream_t stream) {
+    PlanArgs pa{};
     pa.a = a;
     pa.n_pairs = n_pairs;
     pa.buckets = cfg.persistent ? kBuckets : 1;
     pa.extend = a.rows != nullptr;
     pa.single_max = cfg.single_max;
+    pa.chain = cfg.chain;
+    pa.lim_scale = kItemShare / (64.0f * (float)(cfg.sweep_grid > 0 ? cfg.sweep_grid : 1));
     pa.s = s;
+    if (cfg.chain) pa.sw = *sw;
     pa.band = nullptr;
     return run_plan(pa, stream);
 }
 
 hipError_t launch_band_plan(const PairArrays &a, const int32_t *band, int64_t n_pairs, const PlanScratch &s,
                             hipStream_t stream) {
-    PlanArgs pa;
+    PlanArgs pa{};
     pa.a = a;
     pa.n_pairs = n_pairs;
     pa.buckets = kBuckets;
     pa.extend = 0;
-    pa.single_max = kSingleMaxRegion;
     pa.s = s;
     pa.band = band;
     return run_plan(pa, stream);

@@ -37,6 +37,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(single_waves
 void k_single(PairArrays a, const int32_t *__restrict__ list, const int32_t *__restrict__ count,
               int32_t *queue) {
     const int n_items = *count;
+    if (n_items == 0) return;   // no wave asks the queue (2,048 of them: 20 us)
     int item = blockIdx.x;
     if (queue) {
         int it = 0;

@@ -1,5 +1,5 @@
 // Internal interface between the C ABI (rawalign_abi.cpp) and the kernels
-// (dtw_single.hip, dtw_multi.hip, dtw_antidiag.hip, dtw_plan.hip, dtw_bnb.hip).  Not installed; the public
+// (dtw_sweep.hip, dtw_single.hip, dtw_antidiag.hip, dtw_plan.hip, ...).  Not installed; the public
 // interface is include/rawalign.h.
 #pragma once
 
@@ -15,6 +15,8 @@ namespace ra {
 //   single_hi: one stripe, 34..64 columns per lane (region <= 4096 levels)
 //   multi:     several stripes of at most 256 kMultiMaxK columns swept one
 //              after another by the same wave (region > 4096 levels)
+// In chained batches the first list's counters serve the stripe sweep's items
+// (dtw_sweep.hip) and only queries beyond its edge columns take single_hi.
 // The banded planner (dtw_plan.hip, band mode) uses the same lists for its
 // four pair classes, so there are four lists although plain batches use
 // three.
@@ -59,6 +61,49 @@ constexpr int kEdgeCap = 16384;                        // longest query of a mul
 // Number of LPT buckets per route: cells are bucketed by quarter octaves.
 constexpr int kBuckets = 192;
 
+// The stripe sweep (dtw_sweep.hip): widest lane, resident waves per SIMD.
+constexpr int kSweepMaxC = 32;
+constexpr int kSweepWaves = 5;
+constexpr int kSweepStripe = 64 * kSweepMaxC;   // 2048 columns
+// Narrowest lane the planner picks to spread few or long pairs.
+constexpr int kSweepMinC = 7;
+// One ring slot: the corner, a value per row, the running minimum and column.
+constexpr int kSlotFloats = kEdgeCap + 64;
+constexpr int kOwnFloats = kEdgeCap;   // a wave's own edge column: the rows alone
+// Work item of the chained sweep: pair, columns per lane, stripes per item,
+// this item and the items of the pair.
+struct ItemCode {
+    int p, c, k, i, items;
+};
+RA_HOST_DEV constexpr uint64_t pack_item(ItemCode x) {
+    return (uint64_t)x.p | ((uint64_t)x.c << 31) | ((uint64_t)x.k << 37) | ((uint64_t)x.i << 46) | ((uint64_t)x.items << 55);
+}
+RA_HOST_DEV constexpr ItemCode unpack_item(uint64_t u) {
+    return {(int)(u & 0x7fffffff), (int)(u >> 31 & 0x3f), (int)(u >> 37 & 0x1ff), (int)(u >> 46 & 0x1ff), (int)(u >> 55)};
+}
+constexpr int kMaxItems = kMaxRegion / (64 * kSweepMinC) + 1;
+static_assert(kSweepMaxC < 64 && kMaxItems < 512 && kMaxRegion / kSweepStripe < 512, "item fields");
+
+// Work-queue heads, each in a cache line of its own: additions to one address
+// take 11 ns each however many waves make them, which with one head and the
+// failure flag beside it was 0.95 ms of 1.0 for 20,000 pairs of 180 events.
+constexpr int kQueues = 8;
+constexpr int kQueueStride = 32;
+
+// Scratch of the chained sweep.
+struct SweepScratch {
+    uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
+    int64_t item_cap;
+    int32_t *n_items;
+    int32_t *queue;       // [kQueues * kQueueStride] work-queue heads
+    float *ring;          // [ring_slots * kSlotFloats] edge columns between items
+    float *own;           // [grid * kOwnFloats] edge columns within an item
+    int ring_slots;
+    int32_t *done;        // [ring_slots] item after the one whose column was consumed last
+    int32_t *failed;      // a wait timed out: the next planner refills the ring
+    double *partial;      // [kPlanGrid] cells of each planning workgroup's pairs
+};
+
 // Per-stream planning scratch (device memory).
 struct PlanScratch {
     int32_t *hist;      // [kNumRoutes * kBuckets] histogram, then cursors
@@ -66,7 +111,7 @@ struct PlanScratch {
     int32_t *queue;     // [kNumRoutes]  persistent work-queue heads
     int32_t *list;      // [kNumRoutes * capacity] pair indices per route
     int64_t capacity;   // pairs the lists can hold
-    float *edge;        // [multi_grid * kEdgeCap] stripe edge columns, one slot per wave
+    float *edge;        // stripe edge columns of kEdgeCap floats, one slot per wave
     float *rowbuf;      // [antidiag_grid * kMaxRegion] anti-diagonal kernel row buffers (or null)
 };
 
@@ -160,19 +205,22 @@ struct BnbArgs {
 
 struct LaunchCfg {
     bool persistent;    // atomic queue + LPT order (else static assignment, arrival order)
-    int lo_grid;        // grid sizes (workgroups of one wave)
+    bool chain;         // the stripe sweep takes every pair but over-long queries
+    int sweep_grid;     // grid sizes (workgroups of one wave); waves of the sweep resident at once
+    int lo_grid;
     int hi_grid;
-    int multi_grid;     // workgroups of the multi-stripe route (one wave, or pipe_waves in the pipeline); also
-                        // the number of edge slots
+    int multi_grid;     // also the number of edge slots
     int antidiag_grid;  // workgroups of the anti-diagonal kernel (256 threads)
     int single_max = kSingleMaxRegion;   // widest region of the single-stripe routes (2048 or 4096)
 };
 
-// Waves sharing a pair in the pipelined multi-stripe kernel (dtw_pipe.hip).
-constexpr int kPipeMaxWaves = 8;
-
+// Workgroups of the planning kernels (each takes a contiguous range of
+// pairs), so a batch of millions of pairs still adds each busy bin to the
+// global histogram only a few hundred times.
+constexpr int kPlanGrid = 512;
 hipError_t launch_plan(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg,
-                       const PlanScratch &s, hipStream_t stream);
+                       const PlanScratch &s, const SweepScratch *sw, hipStream_t stream);
+hipError_t launch_sweep(const PairArrays &a, int grid, const SweepScratch &sw, hipStream_t stream);
 hipError_t launch_single_lo(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg,
                             const PlanScratch &s, hipStream_t stream);
 hipError_t launch_single_hi(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg,
@@ -181,11 +229,6 @@ hipError_t launch_multi(const PairArrays &a, int64_t n_pairs, const LaunchCfg &c
                         const PlanScratch &s, hipStream_t stream);
 hipError_t launch_antidiag(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg,
                            const PlanScratch &s, hipStream_t stream);
-// Multi-stripe route on workgroups of `waves` waves (2, 4 or 8) sharing each
-// pair, stripes pipelined (dtw_pipe.hip).
-hipError_t launch_pipe(int waves, const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg,
-                       const PlanScratch &s, hipStream_t stream);
-int pipe_blocks_per_cu(int waves, bool extend);
 hipError_t launch_bnb(const BnbArgs &b, int grid, float *edge, hipStream_t stream);
 int bnb_blocks_per_cu();
 // per_candidate: n_events holds one count per candidate (anchored chains)
@@ -234,6 +277,7 @@ constexpr size_t kNoallocScratchBytes =
 hipError_t noalloc_scratch(int dev, PlanScratch &out);
 
 // Occupancy-derived resident workgroups per CU of each route's kernel.
+int sweep_blocks_per_cu(bool extend);
 int single_lo_blocks_per_cu(bool extend);
 int single_hi_blocks_per_cu(bool extend);
 int multi_blocks_per_cu(bool extend);

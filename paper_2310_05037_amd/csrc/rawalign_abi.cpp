@@ -54,6 +54,11 @@ struct StreamScratch {
     int64_t edge_slots = 0;
     float *rowbuf = nullptr;    // anti-diagonal kernel only
     int64_t row_slots = 0;
+    int32_t *sweep_words = nullptr;   // chained sweep: partial cells | counters | slot counters
+    uint64_t *items = nullptr;
+    int64_t item_cap = 0;
+    float *ring = nullptr;
+    int64_t ring_slots = 0;
     int32_t *tiny_words = nullptr;   // one-pair-per-lane planning: hist | counts | base
     ra::TinyRec *tiny_list = nullptr;
     int64_t tiny_capacity = 0;
@@ -183,6 +188,78 @@ int get_scratch(int dev, hipStream_t stream, int64_t n_pairs, int64_t edge_slots
     }
     out = &s;
     return RAWALIGN_OK;
+}
+
+// Scratch of the chained sweep: work items, the ring of edge columns (filled
+// with its empty mark on `stream`, ahead of the kernels) and its counters.
+constexpr int64_t kMaxRing = 8192;
+int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ring_slots, ra::SweepScratch &out) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    hipError_t e;
+    const size_t line = ra::kQueueStride * sizeof(int32_t);
+    const size_t head = ra::kPlanGrid * sizeof(double) + (1 + ra::kQueues) * line;
+    if (!s.sweep_words) {
+        e = hipMalloc((void **)&s.sweep_words, head + kMaxRing * sizeof(int32_t));
+        if (e != hipSuccess) {
+            s.sweep_words = nullptr;
+            return alloc_fail(e);
+        }
+        e = hipMemsetAsync(s.sweep_words, 0, head + kMaxRing * sizeof(int32_t), stream);
+        if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
+    }
+    if (s.item_cap < item_cap) {
+        const int64_t cap = std::max(item_cap, s.item_cap * 2);
+        if (s.items) (void)hipFree(s.items);
+        s.items = nullptr;
+        s.item_cap = 0;
+        e = hipMalloc((void **)&s.items, (size_t)cap * sizeof(uint64_t));
+        if (e != hipSuccess) {
+            s.items = nullptr;
+            return alloc_fail(e);
+        }
+        s.item_cap = cap;
+    }
+    if (s.ring_slots < ring_slots) {
+        if (s.ring) (void)hipFree(s.ring);
+        s.ring = nullptr;
+        s.ring_slots = 0;
+        const size_t bytes = (size_t)ring_slots * ra::kSlotFloats * sizeof(float);
+        e = hipMalloc((void **)&s.ring, bytes);
+        if (e != hipSuccess) {
+            s.ring = nullptr;
+            return alloc_fail(e);
+        }
+        e = hipMemsetAsync(s.ring, 0xff, bytes, stream);
+        if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
+        s.ring_slots = ring_slots;
+    }
+    out.partial = (double *)s.sweep_words;
+    out.n_items = (int32_t *)(out.partial + ra::kPlanGrid);
+    out.failed = out.n_items + 1;
+    out.queue = out.n_items + ra::kQueueStride;
+    out.done = out.queue + ra::kQueues * ra::kQueueStride;
+    out.items = s.items;
+    out.item_cap = s.item_cap;
+    out.ring = s.ring;
+    out.ring_slots = (int)s.ring_slots;
+    return RAWALIGN_OK;
+}
+
+// The sweep's scratch can be had: it is there, or the stream is not being
+// captured.  A captured call that would have to allocate it takes the routes
+// that need none.
+bool sweep_ready(int dev, hipStream_t stream, int64_t item_cap, int64_t ring_slots) {
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        const StreamScratch &s = g_scratch[{dev, stream}];
+        if (s.item_cap >= item_cap && s.ring_slots >= ring_slots) return true;
+    }
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st == hipStreamCaptureStatusNone;
 }
 
 // Planning scratch of the one-pair-per-lane kernel (global calls only).
@@ -335,28 +412,49 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     if (rc) return rc;
 
     const bool ext = c.rows != nullptr;
-    // The pipelined kernel takes forward subsequence alignments (plain and
-    // streaming); global and reversed passes keep the single-wave kernel.
-    const bool pipeline = o.long_kernel == RAWALIGN_LONG_PIPELINE && c.bound == ra::kBoundSubseq && !c.reverse;
-    const int pipe_waves = o.pipe_waves ? o.pipe_waves : 4;
+    const bool antidiag = o.long_kernel == RAWALIGN_LONG_ANTIDIAG;
+    const bool tiny = c.bound == ra::kBoundGlobal && !c.reverse;
+    const int64_t levels = std::min<int64_t>(c.r_size, ra::kMaxRegion);
     ra::LaunchCfg cfg;
     cfg.persistent = o.mode == RAWALIGN_MODE_PERSISTENT;
+    // Persistent batches are swept stripe by stripe (dtw_sweep.hip).  A wave
+    // takes whole pairs in plain ones (a static assignment), where nothing may
+    // be allocated, beside the anti-diagonal kernel, and for gaps between
+    // anchors: few hundred events against one or two columns per lane, where
+    // two rows a step double the skew (the call on 100,000 chains took 0.51 ms
+    // against 0.46).  Work items of all pairs: at most one per full stripe of
+    // each, and as many narrower ones as the planner's share per resident wave
+    // allows.
+    const int64_t full_stripes = c.n_pairs * ((levels + ra::kSweepStripe - 1) / ra::kSweepStripe + 1);
+    cfg.chain = cfg.persistent && !tiny && !noalloc && !antidiag && full_stripes < ((int64_t)1 << 28);
     cfg.single_max = o.single_max ? o.single_max : ra::kSingleMaxRegion;
-    cfg.lo_grid = grid_of(info.cus, o.lo_waves_per_cu, ra::single_lo_blocks_per_cu(ext));
-    cfg.hi_grid = grid_of(info.cus, o.hi_waves_per_cu, ra::single_hi_blocks_per_cu(ext));
-    if (pipeline)   // workgroups of pipe_waves waves; long_waves_per_cu counts waves
-        cfg.multi_grid = info.cus * (o.long_waves_per_cu ? std::max(1, o.long_waves_per_cu / pipe_waves)
-                                                         : ra::pipe_blocks_per_cu(pipe_waves, ext));
-    else
+    cfg.lo_grid = cfg.multi_grid = cfg.sweep_grid = 0;
+    int64_t ring = 0, item_cap = 0;
+    if (cfg.chain) {
+        // One kernel takes all three routes: the widest of their grids.
+        const int occ = ra::sweep_blocks_per_cu(ext);
+        const int w[3] = {o.lo_waves_per_cu, o.hi_waves_per_cu, o.long_waves_per_cu};
+        const bool full = !w[0] || !w[1] || !w[2];
+        const int64_t narrow = 64 * ra::kSweepMinC;
+        cfg.sweep_grid = info.cus * (full ? occ : std::min(occ, std::max({w[0], w[1], w[2]})));
+        cfg.sweep_grid = (int)std::min<int64_t>(cfg.sweep_grid, c.n_pairs * ((levels + narrow - 1) / narrow + 1));
+        ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)cfg.sweep_grid));
+        item_cap = full_stripes + 3 * (int64_t)cfg.sweep_grid;
+        cfg.chain = sweep_ready(dev, c.stream, item_cap, ring);
+    }
+    if (!cfg.chain) {
+        cfg.lo_grid = grid_of(info.cus, o.lo_waves_per_cu, ra::single_lo_blocks_per_cu(ext));
         cfg.multi_grid = grid_of(info.cus, o.long_waves_per_cu, ra::multi_blocks_per_cu(ext));
+    }
+    cfg.hi_grid = grid_of(info.cus, o.hi_waves_per_cu, ra::single_hi_blocks_per_cu(ext));
     // Anti-diagonal kernel: opts.long_waves_per_cu counts its workgroups per
     // CU; by default its occupancy limit (5: LDS and registers), each with a
     // 256 KiB row buffer.
     const int ad_occ = ra::antidiag_blocks_per_cu();
     cfg.antidiag_grid = info.cus * (o.long_waves_per_cu ? std::min(o.long_waves_per_cu, ad_occ) : ad_occ);
     // A persistent grid never needs more workgroups than the batch has pairs
-    // (a small batch would otherwise launch thousands of waves that only
-    // start and exit).
+    // or items (a small batch would otherwise launch thousands of waves that
+    // only start and exit).
     {
         const int cap = (int)std::min<int64_t>(c.n_pairs, 1 << 30);
         cfg.lo_grid = std::min(cfg.lo_grid, cap);
@@ -364,21 +462,27 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         cfg.multi_grid = std::min(cfg.multi_grid, cap);
         cfg.antidiag_grid = std::min(cfg.antidiag_grid, cap);
     }
-    const bool antidiag = o.long_kernel == RAWALIGN_LONG_ANTIDIAG;
 
     const bool timing = (o.flags & RAWALIGN_FLAG_TIMING) != 0;
-    const bool concurrent = o.streams == 3;
+    const bool concurrent = o.streams == 3 && !cfg.chain;
     StreamScratch *s = nullptr;
     ra::PlanScratch fixed;
+    ra::SweepScratch sw{};
     if (noalloc) {
         const hipError_t e = ra::noalloc_scratch(dev, fixed);
         if (e != hipSuccess) return hip_fail(e, "allocation-free scratch (hipGetSymbolAddress)");
         // One edge slot per resident multi-stripe wave.
         cfg.multi_grid = std::min(cfg.multi_grid, ra::kNoallocEdgeSlots);
     } else {
-        rc = get_scratch(dev, c.stream, c.n_pairs, cfg.multi_grid, antidiag ? cfg.antidiag_grid : 0, timing,
-                         concurrent, s);
+        // Edge columns of the waves: the multi-stripe kernel's, or the sweep's own.
+        const int columns = !cfg.chain ? cfg.multi_grid : levels > ra::kSweepStripe ? cfg.sweep_grid : 0;
+        rc = get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing, concurrent, s);
         if (rc) return rc;
+        if (cfg.chain) {
+            rc = get_sweep(*s, c.stream, item_cap, ring, sw);
+            if (rc) return rc;
+            sw.own = s->edge;
+        }
     }
 
     ra::PairArrays a;
@@ -399,7 +503,6 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     a.bound = c.bound;
     a.reverse = c.reverse ? 1 : 0;
     const ra::PlanScratch ps = noalloc ? fixed : plan_view(*s);
-    const bool tiny = c.bound == ra::kBoundGlobal && !c.reverse;
     if (tiny) {
         rc = get_tiny(*s, c.n_pairs);
         if (rc) return rc;
@@ -424,7 +527,7 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     };
     if (timing && (e = hipEventRecord(s->ev[0], c.stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (split && (rc = fork()) != RAWALIGN_OK) return rc;
-    e = ra::launch_plan(a, c.n_pairs, cfg, ps, c.stream);
+    e = ra::launch_plan(a, c.n_pairs, cfg, ps, &sw, c.stream);
     if (e != hipSuccess) return hip_fail(e, "plan kernels");
     if (tiny) {
         e = ra::launch_tiny_plan(a, c.n_pairs, tiny_view(*s), st[0]);
@@ -444,22 +547,26 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         if (e != hipSuccess) return hip_fail(e, "one-pair-per-lane kernels");
     }
     const hipStream_t route_st[3] = {split ? c.stream : st[0], split ? c.stream : st[1], split ? c.stream : st[2]};
-    // Longest regions first: they bound the makespan.
-    const char *names[3] = {antidiag ? "anti-diagonal kernel" : pipeline ? "pipelined multi-stripe kernel"
-                                                                         : "multi-stripe kernel",
+    // Longest regions first: they bound the makespan.  The sweep takes regions
+    // of every width and is timed as the long route.
+    const char *names[3] = {antidiag ? "anti-diagonal kernel" : cfg.chain ? "stripe sweep" : "multi-stripe kernel",
                             "single-stripe kernel (34-64 columns per lane)",
                             "single-stripe kernel (2-32 columns per lane)"};
     const int ev_slot[3] = {6, 4, 2};   // long, hi, lo
+    // With the sweep, the one route left is for queries beyond an edge column:
+    // they can only be there if q holds as many events.
+    const bool hi = !cfg.chain || (c.q_size > ra::kEdgeCap && c.r_size > ra::kSweepStripe);
     for (int i = 0; i < 3; ++i) {
         const hipStream_t rs = route_st[i];
         if (timing) (void)hipEventRecord(s->ev[ev_slot[i]], rs);
+        e = hipSuccess;
         if (i == 0)
-            e = antidiag ? ra::launch_antidiag(a, c.n_pairs, cfg, ps, rs)
-                : pipeline ? ra::launch_pipe(pipe_waves, a, c.n_pairs, cfg, ps, rs)
-                           : ra::launch_multi(a, c.n_pairs, cfg, ps, rs);
-        else if (i == 1)
+            e = antidiag    ? ra::launch_antidiag(a, c.n_pairs, cfg, ps, rs)
+                : cfg.chain ? ra::launch_sweep(a, cfg.sweep_grid, sw, rs)
+                            : ra::launch_multi(a, c.n_pairs, cfg, ps, rs);
+        else if (i == 1 && hi)
             e = ra::launch_single_hi(a, c.n_pairs, cfg, ps, rs);
-        else
+        else if (i == 2 && !cfg.chain)
             e = ra::launch_single_lo(a, c.n_pairs, cfg, ps, rs);
         if (e != hipSuccess) return hip_fail(e, names[i]);
         if (timing) (void)hipEventRecord(s->ev[ev_slot[i] + 1], rs);
@@ -1018,59 +1125,39 @@ int rawalign_autotune(const float *q, int64_t q_size, const int64_t *q_off, cons
         return RAWALIGN_OK;
     };
     // Stage 1, the kernel shape at occupancy-sized grids on one stream: the
-    // single-stripe cut-off (2049..4096-level regions on one stripe of
-    // 34..64 columns per lane at two waves per SIMD, or on two stripes of
-    // 17..32 at four) and the long-route kernel with its workgroup shape
-    // (one wave per pair, 2, 4 or 8 waves sharing each pair, or the
-    // anti-diagonal kernel's 256-thread workgroup; waves = 0 below).
-    for (int single_max : {4096, 2048}) {
-        for (int waves : {1, 2, 4, 8, 0}) {
-            rawalign_opts o;
-            defaults(o);
-            o.single_max = single_max;
-            if (waves > 1) {
-                o.long_kernel = RAWALIGN_LONG_PIPELINE;
-                o.pipe_waves = waves;
-            } else if (waves == 0) {
-                o.long_kernel = RAWALIGN_LONG_ANTIDIAG;
-            }
-            rc = consider(o);
-            if (rc) break;
-        }
+    // stripe sweep for every region, or the anti-diagonal kernel's 256-thread
+    // workgroup above a cut-off of 4096 or 2048 levels.
+    for (int kind = 0; kind < 3; ++kind) {
+        rawalign_opts o;
+        defaults(o);
+        o.single_max = kind == 2 ? 2048 : 4096;
+        if (kind > 0) o.long_kernel = RAWALIGN_LONG_ANTIDIAG;
+        rc = consider(o);
         if (rc) break;
     }
-    // Stage 2, at that shape: concurrent or sequential route kernels, and
-    // persistent grids at or below each kernel's occupancy limit (waves per
-    // CU; the pipelined kernel counts its waves, the anti-diagonal kernel
-    // its workgroups).
+    // Stage 2, at that shape: the persistent grid at or below occupancy
+    // (waves per CU; the anti-diagonal kernel counts its workgroups, and may
+    // run beside the sweep on three streams).
     if (!rc) {
         const rawalign_opts shape = best;
-        const bool pipe = shape.long_kernel == RAWALIGN_LONG_PIPELINE;
         const bool antidiag = shape.long_kernel == RAWALIGN_LONG_ANTIDIAG;
-        const int pw = shape.pipe_waves ? shape.pipe_waves : 4;
-        const int lo_occ = ra::single_lo_blocks_per_cu(false);
-        const int hi_occ = ra::single_hi_blocks_per_cu(false);
-        const int mu_occ = pipe       ? ra::pipe_blocks_per_cu(pw, false) * pw
-                           : antidiag ? ra::antidiag_blocks_per_cu()
-                                      : ra::multi_blocks_per_cu(false);
-        const int mu_less = pipe ? mu_occ - pw : antidiag ? mu_occ - 1 : mu_occ - 4;
+        const int occ = ra::sweep_blocks_per_cu(false);
+        const int ad_occ = ra::antidiag_blocks_per_cu();
         std::vector<rawalign_opts> cands;
         for (int streams : {1, 3})
-            for (int lo : {lo_occ, lo_occ > 4 ? lo_occ - 4 : lo_occ})
-                for (int hi : {hi_occ, hi_occ > 4 ? hi_occ - 4 : hi_occ})
-                    for (int mu : {mu_occ, mu_less > 0 ? mu_less : mu_occ}) {
-                        rawalign_opts o = shape;
-                        o.streams = streams;
-                        o.lo_waves_per_cu = lo;
-                        o.hi_waves_per_cu = hi;
-                        o.long_waves_per_cu = mu;
-                        bool dup = false;
-                        for (const rawalign_opts &x : cands)
-                            dup = dup || (x.streams == o.streams && x.lo_waves_per_cu == o.lo_waves_per_cu &&
-                                          x.hi_waves_per_cu == o.hi_waves_per_cu &&
-                                          x.long_waves_per_cu == o.long_waves_per_cu);
-                        if (!dup) cands.push_back(o);
-                    }
+            for (int less : {0, 1}) {
+                rawalign_opts o = shape;
+                o.streams = streams;
+                o.lo_waves_per_cu = o.hi_waves_per_cu = o.long_waves_per_cu = std::max(1, occ - 4 * less);
+                if (antidiag) {
+                    o.lo_waves_per_cu = occ;
+                    o.hi_waves_per_cu = 0;
+                    o.long_waves_per_cu = std::max(1, ad_occ - less);
+                } else if (streams == 3) {
+                    continue;
+                }
+                cands.push_back(o);
+            }
         for (const rawalign_opts &o : cands) {
             rc = consider(o);
             if (rc) break;

@@ -71,7 +71,7 @@ hipError_t launch(int blocks, int iters, float *sink, uint64_t *cycles) {
     return hipGetLastError();
 }
 
-// One thread reads the constant-rate clock that the pipelined kernels'
+// One thread reads the constant-rate clock that the chained kernels'
 // capped waits measure time with, and the shader cycle counter.
 __global__ void k_clock(uint64_t *out) {
     if (threadIdx.x == 0) {
