@@ -184,10 +184,14 @@ struct BnbScratch {
     int32_t *read_of;     // [n_pairs] read owning the pair, -1 none, -2 several
     uint8_t *status;      // [n_pairs] BnbStatus
     uint64_t *best;       // [n_reads] best Score so far, order-preserving key
-    int32_t *list;        // [n_pairs] pairs to align: first candidates, then the others, longest first
-    int32_t *hist;        // [2 * kBuckets] histogram, then cursors
-    int32_t *counts;      // [2] pairs per group
-    int32_t *queue;       // work-queue head
+    // This round's part of every pair: its events, first row (-1: none),
+    // whether that is row 0, and the sweep's minimum and column of its last row.
+    int64_t *part_off;
+    int32_t *part_len;
+    int32_t *part_row;
+    uint8_t *part_first;
+    float *part_score;
+    int32_t *part_end;
 };
 
 struct BnbArgs {
@@ -199,7 +203,6 @@ struct BnbArgs {
     int64_t n_reads;
     double b_match;
     int max_query;
-    int block_rows;
     BnbScratch s;
 };
 
@@ -229,8 +232,10 @@ hipError_t launch_multi(const PairArrays &a, int64_t n_pairs, const LaunchCfg &c
                         const PlanScratch &s, hipStream_t stream);
 hipError_t launch_antidiag(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cfg,
                            const PlanScratch &s, hipStream_t stream);
-hipError_t launch_bnb(const BnbArgs &b, int grid, float *edge, hipStream_t stream);
-int bnb_blocks_per_cu();
+// Early termination: set up round 0 (block_rows events of most pairs); after a
+// round, settle it and, with rounds left, set up the next one.
+hipError_t launch_bnb_start(const BnbArgs &b, int block_rows, hipStream_t stream);
+hipError_t launch_bnb_next(const BnbArgs &b, int block_rows, int left, hipStream_t stream);
 // per_candidate: n_events holds one count per candidate (anchored chains)
 // instead of one per read.
 hipError_t launch_decide(const float *score, int64_t n_pairs, const int64_t *cand_off, const int32_t *cand_cnt,

@@ -362,6 +362,7 @@ struct Call {
     hipStream_t stream;
     int bound = ra::kBoundSubseq;   // ra::BoundMode
     bool reverse = false;           // query and region read back to front
+    int64_t max_query = INT64_MAX;  // no query is longer
 };
 
 int check_call(const Call &c) {
@@ -555,7 +556,7 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     const int ev_slot[3] = {6, 4, 2};   // long, hi, lo
     // With the sweep, the one route left is for queries beyond an edge column:
     // they can only be there if q holds as many events.
-    const bool hi = !cfg.chain || (c.q_size > ra::kEdgeCap && c.r_size > ra::kSweepStripe);
+    const bool hi = !cfg.chain || (std::min(c.q_size, c.max_query) > ra::kEdgeCap && c.r_size > ra::kSweepStripe);
     for (int i = 0; i < 3; ++i) {
         const hipStream_t rs = route_st[i];
         if (timing) (void)hipEventRecord(s->ev[ev_slot[i]], rs);
@@ -744,25 +745,21 @@ int rawalign_map_bnb(const float *q, int64_t q_size, const int64_t *q_off, const
             b.pairs = b.reads = 0;
             const int64_t P = std::max(np, 2 * b.pairs), R = std::max(nr, 2 * b.reads);
             // 8-byte fields first, then 4-byte, then 1-byte: every field stays aligned.
-            const size_t words = 2 * ra::kBuckets + 4;
-            const size_t bytes = (size_t)R * 8 + (size_t)P * 8 + words * 4 + (size_t)P + 256;
+            const size_t bytes = (size_t)R * 8 + (size_t)P * (8 + 5 * 4 + 2);
             hipError_t e = hipMalloc(&b.mem, bytes);
             if (e != hipSuccess) {
                 b.mem = nullptr;
                 return alloc_fail(e);
             }
-            char *m = (char *)b.mem;
-            b.view.best = (uint64_t *)m;
-            m += (size_t)R * 8;
-            b.view.read_of = (int32_t *)m;
-            m += (size_t)P * 4;
-            b.view.list = (int32_t *)m;
-            m += (size_t)P * 4;
-            b.view.hist = (int32_t *)m;
-            b.view.counts = b.view.hist + 2 * ra::kBuckets;
-            b.view.queue = b.view.counts + 2;
-            m += words * 4;
-            b.view.status = (uint8_t *)m;
+            b.view.best = (uint64_t *)b.mem;
+            b.view.part_off = (int64_t *)(b.view.best + R);
+            b.view.read_of = (int32_t *)(b.view.part_off + P);
+            b.view.part_len = b.view.read_of + P;
+            b.view.part_row = b.view.part_len + P;
+            b.view.part_end = b.view.part_row + P;
+            b.view.part_score = (float *)(b.view.part_end + P);
+            b.view.status = (uint8_t *)(b.view.part_score + P);
+            b.view.part_first = b.view.status + P;
             b.pairs = P;
             b.reads = R;
         }
@@ -791,18 +788,27 @@ int rawalign_map_bnb(const float *q, int64_t q_size, const int64_t *q_off, const
     ba.n_reads = n_reads;
     ba.b_match = b_match;
     ba.max_query = max_query;
-    ba.block_rows = block_rows;
     ba.s = sc;
 
     hipError_t e;
     if (n_pairs > 0) {
-        // One persistent wave per resident slot, each with its own stripe edge slot.
-        const int grid = (int)std::min<int64_t>(grid_of(info.cus, o.long_waves_per_cu, ra::bnb_blocks_per_cu()),
-                                                n_pairs);
-        StreamScratch *ss = nullptr;
-        rc = get_scratch(dev, st, n_pairs, grid, 0, false, false, ss);
-        if (rc) return rc;
-        if ((e = ra::launch_bnb(ba, grid, ss->edge, st)) != hipSuccess) return hip_fail(e, "early-termination kernels");
+        if ((e = ra::launch_bnb_start(ba, block_rows, st)) != hipSuccess) return hip_fail(e, "early-termination kernels");
+        // Rounds after the first: as many as doublings of block_rows up to the
+        // longest query, at most five; the last one ends every pair.
+        int left = 0;
+        for (int64_t rows = block_rows; rows < max_query && left < 5; rows *= 2) ++left;
+        o.mode = RAWALIGN_MODE_PERSISTENT;
+        o.long_kernel = RAWALIGN_LONG_STRIPED;
+        o.lo_waves_per_cu = o.hi_waves_per_cu = o.long_waves_per_cu;
+        const Call part{q, q_size, sc.part_off, sc.part_len, r, r_size, r_off, r_len, n_pairs, sc.part_score,
+                        sc.part_end, rows, rows_size, row_off, sc.part_first, st, ra::kBoundSubseq, false, max_query};
+        for (;; --left) {
+            rc = run(part, o);
+            if (rc) return rc;
+            e = ra::launch_bnb_next(ba, block_rows, left, st);
+            if (e != hipSuccess) return hip_fail(e, "early-termination kernels");
+            if (left == 0) break;
+        }
     }
     if (n_reads > 0) {
         e = ra::launch_decide(out_score, n_pairs, cand_off, cand_cnt, n_events, n_reads, b_match, threshold, out_best,
