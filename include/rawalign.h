@@ -324,10 +324,12 @@ int rawalign_dtw_span(const float *q, int64_t q_size, const int64_t *q_off, cons
  *   out_start are inputs, the result of rawalign_dtw_span on the same pairs
  *   (an end or start that no alignment of the pair can have gets -2 in
  *   every entry); the span passes are skipped.
- *   Other arguments, opts and errors as in rawalign_dtw_span; beyond that
- *   call's scratch this entry point allocates nothing.  One wave per pair
- *   records the directions stripe by stripe in the lane-striped order of the
- *   other kernels; one thread per pair then follows them back.
+ *   Other arguments, opts, errors and scratch as in rawalign_dtw_span.  The
+ *   directions are recorded stripe by stripe, the stripes of a long interval by
+ *   several waves at once (in a stream capture before that call's scratch is
+ *   there, by one wave per pair, without scratch), and one wave per pair then
+ *   follows them back.  A sweep given up (see rawalign_dtw_batch) gives -5 in
+ *   every entry.
  */
 int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, const int32_t *q_len,
                       const float *r, int64_t r_size, const int64_t *r_off, const int32_t *r_len,

@@ -1,6 +1,7 @@
 // dtw_plan.hip -- device-side planning (routing, longest-first ordering,
 // sentinels for degenerate or invalid pairs) and the mapping decision.
 #include "dtw_device.h"
+#include "dtw_path.h"
 
 namespace ra {
 
@@ -15,6 +16,8 @@ struct PlanArgs {
     PlanScratch s;
     SweepScratch sw;
     const int32_t *band;   // banded planning (band half-width per pair), else null
+    int paths;             // planning of the direction pass (path), whose intervals are the regions
+    PathArgs path;
 };
 
 // Banded pairs (dtw_band.hip): class 0 for frames of at most kBandLoMaxH*128
@@ -81,6 +84,13 @@ RA_DEV int band_classify(const PlanArgs &pa, int64_t p, int &bucket, float &scor
 // value of a degenerate pair (empty query or empty region).  Returns -2 for
 // a global pair that the one-pair-per-lane kernel aligns (no output here).
 RA_DEV int classify(const PlanArgs &pa, int64_t p, int &bucket, float &score, int &end) {
+    if (pa.paths) {
+        int n = 0, s = 0, L = 0;
+        if (path_interval(pa.path, p, n, s, L) != 0) return -2;   // the trace writes its sentinel
+        const int b = (int)(4.0f * __log2f((float)n * (float)(L + 64) + 1.0f));
+        bucket = kBuckets - 1 - (b >= kBuckets ? kBuckets - 1 : b);
+        return kRouteSingleLo;
+    }
     if (pa.band) return band_classify(pa, p, bucket, score, end);
     const PairArrays &a = pa.a;
     const int n = a.q_len[p];
@@ -164,6 +174,13 @@ RA_DEV double block_sum(double v) {
 RA_DEV int list_slots(const PlanArgs &pa, int64_t p, int route, float lim, int &k, int &c) {
     if (!pa.chain || route != kRouteSingleLo) return 1;
     int items;
+    if (pa.paths) {
+        int n = 0, s = 0, L = 0;
+        (void)path_interval(pa.path, p, n, s, L);
+        k = 1;
+        path_shape(n, L, lim, items, c);
+        return items;
+    }
     sweep_shape(pa.a.q_len[p], pa.a.r_len[p], lim, items, k, c);
     return items;
 }
@@ -180,7 +197,12 @@ RA_DEV void write_slots(const PlanArgs &pa, int64_t p, int route, int slots, int
 // Phase 0 of a planning workgroup: cells of the pairs [lo, hi).
 RA_DEV double plan_cells(const PlanArgs &pa, int64_t lo, int64_t hi) {
     double cells = 0.0;
-    if (pa.chain) {
+    if (pa.paths) {
+        for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
+            int n = 0, s = 0, L = 0;
+            if (path_interval(pa.path, p, n, s, L) == 0) cells += (double)n * (double)L;
+        }
+    } else if (pa.chain) {
         for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock)
             if (slices_ok(pa.a, p, pa.extend != 0)) cells += (double)pa.a.q_len[p] * (double)pa.a.r_len[p];
     }
@@ -380,6 +402,20 @@ hipError_t launch_plan(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cf
     pa.s = s;
     if (cfg.chain) pa.sw = *sw;
     pa.band = nullptr;
+    return run_plan(pa, stream);
+}
+
+hipError_t launch_path_plan(const PathArgs &path, int grid, const PlanScratch &s, const SweepScratch &sw,
+                            hipStream_t stream) {
+    PlanArgs pa{};
+    pa.n_pairs = path.n_pairs;
+    pa.buckets = kBuckets;
+    pa.chain = 1;
+    pa.lim_scale = kItemShare / (64.0f * (float)grid);
+    pa.s = s;
+    pa.sw = sw;
+    pa.paths = 1;
+    pa.path = path;
     return run_plan(pa, stream);
 }
 

@@ -958,7 +958,32 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
     pa.path_lo = path_lo;
     pa.path_hi = path_hi;
     pa.path_size = path_size;
-    hipError_t e = ra::launch_path(pa, (hipStream_t)stream);
+    int dev = 0;
+    DeviceInfo info;
+    rc = device_info(dev, info);
+    if (rc) return rc;
+    const hipStream_t st = (hipStream_t)stream;
+    // Items: one per pair, one per 2,048 columns and what the planner's share
+    // adds (path_shape: c is at most twice the least).
+    const int64_t levels = std::min<int64_t>(r_size, ra::kMaxRegion);
+    const int grid = (int)std::min<int64_t>((int64_t)info.cus * ra::path_blocks_per_cu(), n_pairs * (levels / 256 + 1));
+    const int64_t item_cap = n_pairs * (levels / ra::kSweepStripe + 2) + 3 * (int64_t)grid;
+    const int64_t ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)grid));
+    ra::SweepScratch sw{};
+    // Past the queue's range, and in a capture before the scratch is there, one
+    // wave per pair.
+    if (item_cap >= ((int64_t)1 << 28) || !sweep_ready(dev, st, item_cap, ring)) {
+        const hipError_t e = ra::launch_path(pa, (int)n_pairs, sw, st);
+        return e == hipSuccess ? RAWALIGN_OK : hip_fail(e, "path kernels");
+    }
+    StreamScratch *s = nullptr;
+    rc = get_scratch(dev, st, 0, 0, 0, false, false, s);
+    if (rc) return rc;
+    rc = get_sweep(*s, st, item_cap, ring, sw);
+    if (rc) return rc;
+    hipError_t e = ra::launch_path_plan(pa, grid, plan_view(*s), sw, st);
+    if (e != hipSuccess) return hip_fail(e, "path planning");
+    e = ra::launch_path(pa, grid, sw, st);
     if (e != hipSuccess) return hip_fail(e, "path kernels");
     return RAWALIGN_OK;
 }
