@@ -352,13 +352,15 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
  *   chained segment: about 3.3 events per level) and 2*min(band, m-1)+1 <=
  *   2048.  Other pairs use frames over the whole region with the cells
  *   outside the band forced to +inf: one stripe up to 2048 levels, else
- *   stripes of up to 2048 columns swept one after another, each over only
- *   the rows the band spends in it.  The pairs are planned on the device
- *   into four classes (band frames up to 512 columns, wider band frames,
- *   one whole-region stripe, several stripes), each taken longest first
- *   from a persistent queue; the class kernels run concurrently on internal
- *   streams joined back to `stream`.  Scratch: that of rawalign_dtw_batch
- *   plus stripe edge slots, per (device, stream).
+ *   stripes of up to 1024 columns, each over only the rows the band spends in
+ *   it.  A pair that costs more than a wave's share of the call is cut into
+ *   such stripes whatever its shape, and several waves sweep them at once.
+ *   The pairs are planned on the device into four classes (band frames up to
+ *   512 columns, wider band frames, one whole-region stripe, several stripes),
+ *   each taken longest first from a persistent queue; the class kernels run
+ *   concurrently on internal streams and `stream`, which waits for the others.
+ *   Scratch: that of rawalign_dtw_batch, per (device, stream).  A sweep given
+ *   up (see rawalign_dtw_batch) ends with NaN, -5 for the pairs it cut.
  *   A query longer than RAWALIGN_MAX_QUERY_LONG against more than 2048
  *   levels with a band wider than 2048 columns (the one shape no class
  *   takes) gets the sentinel NaN, end -4.  A negative band or an invalid

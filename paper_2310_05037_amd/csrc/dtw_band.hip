@@ -26,7 +26,9 @@
 // lists the other pairs in two classes by frame width, longest first; each
 // class kernel takes its list from a persistent queue, and the two run
 // concurrently.
-#include "dtw_device.h"
+#include "dtw_band.h"
+#include "dtw_chain.h"
+#include "dtw_rows.h"
 
 namespace ra {
 
@@ -376,30 +378,127 @@ void k_band_abs(PairArrays a, const int32_t *__restrict__ band, const int32_t *_
     }
 }
 
-// Class 3: regions above 2048 levels that the band-relative frame does not
-// take (more levels than events, or a band wider than 2048 columns).  One
-// wave sweeps the region stripe by stripe with the multi-stripe kernel's
-// shape (S = ceil(m / 2048) stripes of 64 C columns) and, as in class 2,
-// forces every cell outside its row's band to +inf.  A stripe over columns
-// [a, b] sweeps only the rows whose band meets it: [i0, i1] with i0 the
-// first row with c(i) >= a - w and i1 the last with c(i) <= b + w.  Its
-// rows before i0 are out of band (+inf; row -1 is the free start, zero),
-// and its rows after i1 reach neither row n-1 nor the next stripe, whose
-// west column reads +inf outside [i0, i1].  Lane 63 stores the stripe's
-// last column of rows [i0, i1] into the wave's edge slot, in place (a row
-// is read by a stripe before that stripe rewrites it).
+// Class 3: pairs that are cut into stripes of 64 C columns, C = 4, 8 or 16
+// (band_shape): those that cost more than their share of the call, as work
+// items that several waves sweep at once (dtw_chain.h), and by one wave the
+// others in regions above 2048 levels that the band-relative frame does not
+// take.  As in class 2 every cell outside its row's band is forced to +inf.  A
+// stripe over columns [a, b] sweeps only the rows whose band meets it: [i0, i1]
+// with i0 the first row with c(i) >= a - w and i1 the last with c(i) <= b + w.
+// Its rows before i0 are out of band (+inf; row -1 is the free start, zero),
+// and its rows after i1 reach neither row n-1 nor the next stripe, whose west
+// column reads +inf outside [i0, i1].
+//
+// What bounds it: the waves of a cut pair wait, those of its later stripes until
+// the band reaches them, and so hold about half of the chip's wave slots idle
+// (4 waves a SIMD, 45 % of the issue slots used on 10,000 uneven pairs of 37 G
+// band cells).  That batch takes 8.1 ms; with one wave per pair it was 28, the
+// longest pair's.  Cells at the band's edges cost 5 instructions, inside it 3.
+// Six waves a SIMD with C up to 8: 10.0 ms (more, narrower stripes to wait
+// for); half the share per item 11.1, twice 9.9.
+
+struct BandRows {   // rows [lo, hi], none if lo > hi
+    int lo, hi;
+};
+
+// First row whose diagonal column reaches X, last row whose diagonal column
+// is at most Y (c(i) = floor(i*m/n) is non-decreasing).
+RA_DEV int first_row_at(int64_t X, int n, int m) { return X <= 0 ? 0 : (int)((X * n + m - 1) / m); }
+RA_DEV int last_row_at(int64_t Y, int n, int m) { return Y < 0 ? -1 : (int)(((Y + 1) * n + m - 1) / m) - 1; }
+
+// Rows of the stripe of `cols` columns from a on; none left or right of the region.
+RA_DEV BandRows stripe_rows(const BandView &bv, int64_t a, int cols) {
+    if (a < 0 || a >= bv.m) return {1, 0};
+    const int64_t b = (a + cols < bv.m ? a + cols : bv.m) - 1;
+    const int lo = first_row_at(a - bv.w, bv.n, bv.m), hi = last_row_at(b + bv.w, bv.n, bv.m);
+    return {lo, hi < bv.n - 1 ? hi : bv.n - 1};
+}
+
+// Rows whose last column a stripe hands to the next one: those the next reads.
+RA_DEV BandRows shared_rows(const BandRows &left, const BandRows &right) {
+    if (left.lo > left.hi || right.lo > right.hi) return {1, 0};
+    const int lo = left.lo > right.lo - 1 ? left.lo : right.lo - 1;
+    return {lo, left.hi < right.hi ? left.hi : right.hi};
+}
+
+// rows2 (dtw_rows.h) with the cells left (L) or right (R) of the band set to
+// +inf: in row x the band is at lane positions [lo0, lo0 + 2w], in row y at
+// [lo1, lo1 + 2w].  With L and R also for lanes whose row y is past the end
+// (`both` false), which keep x.
+template <int C, bool L, bool R>
+RA_DEV void band_rows2(bool both, int lo0, int lo1, int w2, float q0, float q1, float nw, float w0, float w1,
+                       const float (&rv)[C], float (&A)[C], float &xl) {
+    const int hi0 = lo0 + w2, hi1 = lo1 + w2;
+    auto inside = [&](int c, int lo, int hi) {
+        if constexpr (L && R) return (unsigned)(c - lo) <= (unsigned)w2;
+        else if constexpr (L) return c >= lo;
+        else return c <= hi;
+    };
+    const float out = kInf;
+    float xpp = w0, y = w1, above = A[0];
+    float xp = fabsf(q0 - rv[0]) + fminf(fminf(nw, above), w0);
+    xp = inside(0, lo0, hi0) ? xp : out;
+    float dy = q1 - rv[0];
+    float dx = q0 - rv[1];
+    auto put = [&](int c, float m) {   // row y (or x) of column c
+        y = fabsf(dy) + m;
+        if constexpr (L && R) {
+            y = inside(c, lo1, hi1) ? y : out;
+            select_into(A[c], both, xp, y);
+        } else {
+            select_into(A[c], inside(c, lo1, hi1), out, y);
+        }
+        y = A[c];
+    };
+#pragma unroll
+    for (int c = 1; c < C; ++c) {
+        __builtin_amdgcn_sched_barrier(0);
+        const float up = A[c];
+        const float mx = fminf(fminf(above, up), xp);
+        const float my = fminf(fminf(xpp, xp), y);
+        float x = fabsf(dx) + mx;
+        x = inside(c, lo0, hi0) ? x : out;
+        if (c + 1 < C) dx = q0 - rv[c + 1 < C ? c + 1 : c];
+        put(c - 1, my);
+        dy = q1 - rv[c];
+        above = up;
+        xpp = xp;
+        xp = x;
+    }
+    put(C - 1, fminf(fminf(xpp, xp), y));
+    xl = xp;
+}
+
+// Per-wave LDS: 64 rows of (query event, west value) for lane 0, lane 63's last
+// column of 64 rows, and room for the other lanes' writes beside it.
+struct BandBuf {
+    float feed[(64 + 2) * 2];
+    float out[64];
+    float sink[63 * 2 + 64];
+};
+constexpr int kBandBlock = 32;   // steps of two rows
+
+// One stripe, two rows a step as in the stripe sweep.  in / out: edge columns,
+// element i for row i; chain: slots of the ring, else the wave's own column (a
+// row is read at least 64 steps before it is written).  best / bj: the stripe's
+// minimum of row n-1.
 template <int C>
-RA_DEV void band_multi_stripe(const BandView &bv, int s, int a, int i0, int i1, int p0, int p1, float *edge,
-                              float &best, int &bj) {
+RA_DEV bool band_stripe(const BandView &bv, int a, const float *in, float *out, bool chain, int32_t *failed, BandBuf *bb,
+                        float &best, int &bj) {
+    best = kInf;
+    bj = 0x7fffffff;
+    const BandRows rows = stripe_rows(bv, a, 64 * C);
+    if (rows.lo > rows.hi) return true;
+    const BandRows west = shared_rows(stripe_rows(bv, (int64_t)a - 64 * C, 64 * C), rows);
+    const BandRows east = shared_rows(rows, stripe_rows(bv, (int64_t)a + 64 * C, 64 * C));
     const int lane = opaque_lane();
     const int n = bv.n, m = bv.m, w = bv.w;
     const int col0 = a + lane * C;
     const __amdgpu_buffer_rsrc_t rrs = make_rsrc(bv.r, m);
-    const __amdgpu_buffer_rsrc_t qrs = make_rsrc(bv.q, n);
-    const __amdgpu_buffer_rsrc_t ers = make_rsrc(edge, n);
-    const int nm1 = n - 1;
+    const int i0 = rows.lo, ns = rows.hi - rows.lo + 1;
     float rv[C], A[C];
-    const float row_before = i0 == 0 ? 0.0f : kInf;   // row i0 - 1 in this stripe
+    float row_before = i0 == 0 ? 0.0f : kInf;   // row i0 - 1 in this stripe
+    asm volatile("" : "+v"(row_before));
 #pragma unroll
     for (int v = 0; v < C; ++v) {
         const int j = col0 + v;
@@ -407,129 +506,205 @@ RA_DEV void band_multi_stripe(const BandView &bv, int s, int a, int i0, int i1, 
         rv[v] = j < m ? lv : kInf;
         A[v] = row_before;
     }
-    // West value of row `row` for lane 0: the previous stripe's last column
-    // inside its rows [p0, p1], else +inf (out of band), row -1 zero.
-    auto west = [&](int row) -> float {
-        const float e = uload(ers, row < 0 ? 0 : row, nm1);
-        if (s == 0) return kInf;
-        return (row >= p0 && row <= p1) ? e : (row == -1 ? 0.0f : kInf);
-    };
-    // c(i) = floor(i*m/n) of this lane's row, from row i0 on.
+    // Lane position of the band's left end in this lane's next row, and
+    // the fraction i*m mod n that carries it on.
     const int64_t im = (int64_t)i0 * m;
-    int c = (int)(im / n), rem = (int)(im % n);
+    int lo = (int)(im / n) - w - col0, rem = (int)(im % n);
     const int qd = m / n, rd = m % n;
-    const int ns = i1 - i0 + 1;
-    float ecur = west(i0 - 1), eprev, qv = 0.0f;
-    float qa = uload(qrs, i0, nm1), qb = uload(qrs, i0 + 1, nm1);
-    float ea = west(i0), eb = west(i0 + 1);
-    const int T = ns + 63;
-    for (int t = 0; t < T; ++t) {
-        const float q0 = qa, e0 = ea;
-        qa = qb;
-        qb = uload(qrs, i0 + t + 2, nm1);
-        ea = eb;
-        eb = west(i0 + t + 2);
-        qv = dpp_shr1(q0, qv);
-        eprev = ecur;
-        ecur = dpp_shr1(e0, A[C - 1]);
-        const bool valid = (unsigned)(t - lane) < (unsigned)ns;
-        const int lo = c - w - col0;   // band of this lane's row in lane positions: [lo, lo + 2w]
-        float diag = eprev, left = ecur;
-#pragma unroll
-        for (int v = 0; v < C; ++v) {
-            const float up = A[v];
-            float nv = fabsf(qv - rv[v]) + fminf(fminf(diag, up), left);
-            nv = (unsigned)(v - lo) <= (unsigned)(2 * w) ? nv : kInf;
-            diag = up;
-            left = nv;
-            A[v] = valid ? nv : A[v];
-        }
-        if (lane == 63 && valid) edge[i0 + t - 63] = A[C - 1];
-        if (valid) {
-            rem += rd;
-            const int carry = rem >= n ? 1 : 0;
-            rem -= carry ? n : 0;
-            c += qd + carry;
-        }
+    auto next_row = [&]() {
+        rem += rd;
+        const int carry = rem >= n ? 1 : 0;
+        rem -= carry ? n : 0;
+        lo += qd + carry;
+    };
+    const bool takes = chain;
+    bool ok = true;
+    // West of row i0 - 1: the free start is zero right of the region's start.
+    float corner = i0 == 0 && a > 0 ? 0.0f : kInf;
+    if (west.lo <= west.hi && west.lo == i0 - 1) {
+        float v = load_agent(in + west.lo);
+        if (chain) ok = take(in, failed, west.lo, lane == 0, v);
+        corner = __shfl(v, 0, 64);
     }
-    best = kInf;
-    bj = 0x7fffffff;
-    if (i1 == n - 1) {
+    const float *const src = west.lo <= west.hi ? in : bv.q;   // nothing to the left: loads of no use
+    float qn, en;
+    auto fetch = [&](int row0) {
+        const int row = row0 + lane < n ? row0 + lane : n - 1;
+        qn = bv.q[row];
+        en = load_agent(src + row);
+    };
+    auto flush = [&](int t0) {   // the block that ended at step t0
+        const int row = i0 + 2 * (t0 - kBandBlock) - 126 + lane;
+        const float v = stored(bb->out[lane]);
+        if (row >= east.lo && row <= east.hi) store_agent(out + row, v);
+    };
+    float xl = 0.0f;
+    typedef float quad __attribute__((ext_vector_type(4)));
+    typedef float pairf __attribute__((ext_vector_type(2)));
+    const quad *feed = reinterpret_cast<const quad *>(bb->feed);
+    quad P{0.0f, kInf, 0.0f, corner}, Q;
+    float *const mine = lane == 63 ? bb->out : bb->sink + 2 * lane;
+    const int steps = (ns + 1) / 2 + 63;
+    fetch(i0);
+    int t0 = 0;
+    for (; t0 < steps; t0 += kBandBlock) {
+        const int row = i0 + 2 * t0 + lane;
+        arrived(qn);
+        arrived(en);
+        const bool from_west = row >= west.lo && row <= west.hi;
+        ok = take(src, failed, row, takes && ok && from_west, en) && ok;
+        reinterpret_cast<pairf *>(bb->feed)[lane] = pairf{qn, from_west ? en : kInf};
+        flush(t0);
+        fetch(i0 + 2 * t0 + 2 * kBandBlock);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // The last row of an odd number of rows is only told apart where it is
+        // row n - 1; elsewhere nothing reads the row after it.
+        const bool odd = (ns & 1) != 0 && rows.hi == n - 1 && 2 * (t0 + kBandBlock) >= ns;
+        pairf *o = reinterpret_cast<pairf *>(mine);
+        int x = 2 * t0 - 2 * lane;
+        Q = feed[0];
+        const quad *f = feed + 1;
+        // P: the previous step's rows; Q: lane 0's of this step, read a step ahead.
+#define RA_BAND_STEP(P, Q, u)                                                                              \
+    {                                                                                                      \
+        const float q0 = dpp_shr1(Q[0], P[0]), q1 = dpp_shr1(Q[2], P[2]);                                  \
+        const float w0 = dpp_shr1(Q[1], xl), w1 = dpp_shr1(Q[3], A[C - 1]);                                \
+        const float nw = P[3];                                                                             \
+        P = f[u];                                                                                          \
+        if ((unsigned)(x + 2 * u) < (unsigned)ns) {                                                        \
+            const int lo0 = lo;                                                                            \
+            next_row();                                                                                    \
+            const int lo1 = lo;                                                                            \
+            next_row();                                                                                    \
+            const bool left = __ballot(lo1 > 0) != 0, right = __ballot(lo0 + 2 * w < C - 1) != 0;          \
+            const bool both = x + 2 * u + 1 < ns;                                                          \
+            if (odd || (left && right))                                                                    \
+                band_rows2<C, true, true>(both, lo0, lo1, 2 * w, q0, q1, nw, w0, w1, rv, A, xl);           \
+            else if (left)                                                                                 \
+                band_rows2<C, true, false>(both, lo0, lo1, 2 * w, q0, q1, nw, w0, w1, rv, A, xl);          \
+            else if (right)                                                                                \
+                band_rows2<C, false, true>(both, lo0, lo1, 2 * w, q0, q1, nw, w0, w1, rv, A, xl);          \
+            else                                                                                           \
+                rows2<C, false>(both, q0, q1, nw, w0, w1, rv, A, xl);                                      \
+        }                                                                                                  \
+        Q = quad{q0, w0, q1, w1};                                                                          \
+        o[u] = pairf{xl, A[C - 1]};                                                                        \
+    }
+#pragma unroll 1
+        for (int u = 0; u < kBandBlock; u += 2, f += 2, o += 2, x += 4) {
+            RA_BAND_STEP(P, Q, 0)
+            RA_BAND_STEP(Q, P, 1)
+        }
+#undef RA_BAND_STEP
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    flush(t0);
+    if (rows.hi == n - 1) {
 #pragma unroll
         for (int v = 0; v < C; ++v)
             if (col0 + v < m) take_min(best, bj, A[v], col0 + v);
     }
     wave_min(best, bj);
+    return ok;
 }
 
-// First row whose diagonal column reaches X, last row whose diagonal column
-// is at most Y (c(i) = floor(i*m/n) is non-decreasing).
-RA_DEV int first_row_at(int64_t X, int n, int m) { return X <= 0 ? 0 : (int)((X * n + m - 1) / m); }
-RA_DEV int last_row_at(int64_t Y, int n, int m) { return Y < 0 ? -1 : (int)(((Y + 1) * n + m - 1) / m) - 1; }
-
+// A work item.  Between items the minimum of row n-1 so far is behind the
+// rows of the edge column.
 template <int C>
-RA_DEV void band_multi_pair(const BandView &bv, int S, float *edge, float &best, int &bj) {
+RA_DEV bool band_item(const BandView &bv, const ItemCode &x, const float *in, float *out, float *own, int32_t *failed,
+                      BandBuf *bb, float &best, int &bj) {
     best = kInf;
     bj = 0x7fffffff;
-    int p0 = 1, p1 = 0;   // the previous stripe's rows (none yet)
-    for (int s = 0; s < S; ++s) {
-        const int a = s * 64 * C;
-        const int b = (a + 64 * C < bv.m ? a + 64 * C : bv.m) - 1;
-        int i0 = first_row_at((int64_t)a - bv.w, bv.n, bv.m);
-        int i1 = last_row_at((int64_t)b + bv.w, bv.n, bv.m);
-        i1 = i1 < bv.n - 1 ? i1 : bv.n - 1;
-        if (i0 > i1) {   // the band does not meet this stripe
-            p0 = 1;
-            p1 = 0;
-            continue;
+    float sb;
+    int sj;
+    if (x.items == 1) {   // the whole region, stripe after stripe
+        for (int a = 0; a < bv.m; a += 64 * C) {
+            (void)band_stripe<C>(bv, a, own, own, false, failed, bb, sb, sj);
+            take_min(best, bj, sb, sj);
+            stores_done();
         }
-        float sb;
-        int sj;
-        band_multi_stripe<C>(bv, s, a, i0, i1, p0, p1, edge, sb, sj);
-        take_min(best, bj, sb, sj);
-        p0 = i0;
-        p1 = i1;
-        // Lane 63's edge stores must be visible to lane 0 of the next stripe.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        return true;
     }
-    if (!(best < kInf)) bj = -1;
+    bool ok = band_stripe<C>(bv, x.i * 64 * C, in, out, true, failed, bb, best, bj);
+    const int lane = __lane_id();
+    if (x.i > 0) {
+        float v = lane < 2 ? load_agent(in + bv.n + lane) : 0.0f;
+        if (ok) ok = take(in, failed, bv.n + lane, lane < 2, v);
+        take_min(best, bj, __shfl(v, 0, 64), __builtin_bit_cast(int, __shfl(v, 1, 64)));
+    }
+    if (x.i + 1 < x.items && lane < 2)
+        store_agent(out + bv.n + lane, lane == 0 ? stored(best) : __builtin_bit_cast(float, bj));
+    return ok;
 }
 
-template <int H>
-RA_DEV void band_multi_dispatch(int h, const BandView &bv, int S, float *edge, float &best, int &bj) {
-    if constexpr (H <= kMultiMaxH) {
-        if (h == H)
-            band_multi_pair<kMultiColStep * H>(bv, S, edge, best, bj);
-        else
-            band_multi_dispatch<H + 1>(h, bv, S, edge, best, bj);
+RA_DEV bool band_item_dispatch(const BandView &bv, const ItemCode &x, const float *in, float *out, float *own,
+                               int32_t *failed, BandBuf *bb, float &best, int &bj) {
+    if (x.c == 4) return band_item<4>(bv, x, in, out, own, failed, bb, best, bj);
+    if (x.c == 8) return band_item<8>(bv, x, in, out, own, failed, bb, best, bj);
+    return band_item<16>(bv, x, in, out, own, failed, bb, best, bj);
+}
+
+RA_DEV BandView band_view(const PairArrays &a, const int32_t *band, int p) {
+    const int m = a.r_len[p];
+    const int w = band[p] < m - 1 ? band[p] : m - 1;
+    return {a.q + a.q_off[p], a.r + a.r_off[p], a.q_len[p], m, w, 2 * w + 1};
+}
+
+RA_DEV void band_result(const PairArrays &a, int p, float best, int bj) {
+    if (__lane_id() == 0) {
+        a.out_score[p] = best;
+        a.out_end[p] = best < kInf || bj == -5 ? bj : -1;
     }
 }
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void k_band_multi(PairArrays a, const int32_t *__restrict__ band, const int32_t *__restrict__ list,
-                  const int32_t *__restrict__ count, int32_t *queue, float *edge_base) {
-    float *edge = edge_base + (size_t)blockIdx.x * kEdgeCap;
+void k_band_chain(PairArrays a, const int32_t *__restrict__ band, SweepScratch sw) {
+    __shared__ __align__(16) BandBuf bb;
+    const int n_items = *sw.n_items;
+    if ((int)blockIdx.x >= n_items) return;
+    float *own = sw.own + (size_t)blockIdx.x * kOwnFloats;
+    for (int t = next_item(sw.queue); t < n_items; t = next_item(sw.queue)) {
+        const ItemCode x = load_item(sw, t);
+        bool ok = open_slots(sw, t, x);
+        float best = kInf;
+        int bj = 0x7fffffff;
+        if (ok) {
+            ok = band_item_dispatch(band_view(a, band, x.p), x, slot_of(sw, t - 1), slot_of(sw, t), own, sw.failed, &bb,
+                                    best, bj);
+            stores_done();   // every kEmpty is back
+            if (x.i > 0) slot_done(sw, t - 1);
+        }
+        if (x.i + 1 == x.items) {
+            if (!ok || (x.items > 1 && gave_up(sw))) {
+                best = __builtin_nanf("");
+                bj = -5;
+            }
+            band_result(a, x.p, best, bj);
+        }
+    }
+}
+
+// Class 3 where there is no chained queue: its list, a pair per wave.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_band_list(PairArrays a, const int32_t *__restrict__ band, const int32_t *__restrict__ list,
+                 const int32_t *__restrict__ count, int32_t *queue, float *edge_base) {
+    __shared__ __align__(16) BandBuf bb;
+    float *own = edge_base + (size_t)blockIdx.x * kOwnFloats;
     const int n_items = *count;
     int it = 0;
     if (__lane_id() == 0) it = atomicAdd(queue, 1);
     int item = __builtin_amdgcn_readfirstlane(it);
     while (item < n_items) {
         const int p = list[item];
-        const int n = a.q_len[p];
-        const int m = a.r_len[p];
-        const int wraw = band[p];
-        const int w = wraw < m - 1 ? wraw : m - 1;
-        const BandView bv{a.q + a.q_off[p], a.r + a.r_off[p], n, m, w, 2 * w + 1};
-        int S, h;
-        stripe_shape(m, S, h, false);
-        float best = __builtin_nanf("");
-        int bj = -2;
-        band_multi_dispatch<kMultiMinH>(h, bv, S, edge, best, bj);
-        if (__lane_id() == 0) {
-            a.out_score[p] = best;
-            a.out_end[p] = bj;
-        }
+        const BandView bv = band_view(a, band, p);
+        ItemCode x{p, 0, 1, 0, 1};
+        (void)band_shape(bv.n, bv.m, bv.w, kInf, x.items, x.c);
+        float best;
+        int bj;
+        (void)band_item_dispatch(bv, x, nullptr, nullptr, own, nullptr, &bb, best, bj);
+        band_result(a, p, best, bj);
         if (__lane_id() == 0) it = atomicAdd(queue, 1);
         item = __builtin_amdgcn_readfirstlane(it);
     }
@@ -540,7 +715,7 @@ void k_band_multi(PairArrays a, const int32_t *__restrict__ band, const int32_t 
 #define RA_BAND_HI k_band<kBandLoMaxH + 1, kBandMaxFrame / 128, 4>
 
 hipError_t launch_band(int cls, const PairArrays &a, const int32_t *band, int grid, const PlanScratch &s,
-                       hipStream_t stream) {
+                       const SweepScratch *sw, hipStream_t stream) {
     const int32_t *list = s.list + cls * s.capacity;
     const int32_t *count = s.counts + cls;
     int32_t *queue = s.queue + cls;
@@ -550,9 +725,10 @@ hipError_t launch_band(int cls, const PairArrays &a, const int32_t *band, int gr
         hipLaunchKernelGGL(RA_BAND_HI, dim3((unsigned)grid), dim3(64), 0, stream, a, band, list, count, queue);
     else if (cls == 2)
         hipLaunchKernelGGL(k_band_abs, dim3((unsigned)grid), dim3(64), 0, stream, a, band, list, count, queue);
-    else   // one edge slot per workgroup: grid <= the slots
-        hipLaunchKernelGGL(k_band_multi, dim3((unsigned)grid), dim3(64), 0, stream, a, band, list, count, queue,
-                           s.edge);
+    else if (sw)   // one edge column per workgroup: grid <= the columns
+        hipLaunchKernelGGL(k_band_chain, dim3((unsigned)grid), dim3(64), 0, stream, a, band, *sw);
+    else
+        hipLaunchKernelGGL(k_band_list, dim3((unsigned)grid), dim3(64), 0, stream, a, band, list, count, queue, s.edge);
     return hipGetLastError();
 }
 
@@ -565,7 +741,7 @@ int band_blocks_per_cu(int cls) {
     else if (cls == 2)
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_band_abs, 64, 0);
     else
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_band_multi, 64, 0);
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_band_chain, 64, 0);
     return nb > 0 ? nb : 1;
 }
 

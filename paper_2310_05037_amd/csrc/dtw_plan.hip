@@ -1,6 +1,6 @@
 // dtw_plan.hip -- device-side planning (routing, longest-first ordering,
 // sentinels for degenerate or invalid pairs) and the mapping decision.
-#include "dtw_device.h"
+#include "dtw_band.h"
 #include "dtw_path.h"
 
 namespace ra {
@@ -18,6 +18,7 @@ struct PlanArgs {
     const int32_t *band;   // banded planning (band half-width per pair), else null
     int paths;             // planning of the direction pass (path), whose intervals are the regions
     PathArgs path;
+    int chain_route;       // the list whose counters the chained queue's items have
 };
 
 // Banded pairs (dtw_band.hip): class 0 for frames of at most kBandLoMaxH*128
@@ -30,7 +31,7 @@ struct PlanArgs {
 // region, NaN/-4 for the one shape left: a query longer than a stripe edge
 // column (kEdgeCap) against more than 2048 levels with a band wider than
 // 2048 columns.
-RA_DEV int band_classify(const PlanArgs &pa, int64_t p, int &bucket, float &score, int &end) {
+RA_DEV int band_classify(const PlanArgs &pa, int64_t p, float lim, int &bucket, float &score, int &end) {
     const PairArrays &a = pa.a;
     const int n = a.q_len[p];
     const int m = a.r_len[p];
@@ -47,6 +48,14 @@ RA_DEV int band_classify(const PlanArgs &pa, int64_t p, int &bucket, float &scor
     }
     const int w = wraw < m - 1 ? wraw : m - 1;
     const int W = 2 * w + 1;
+    int items, c;
+    if (pa.chain && band_shape(n, m, w, lim, items, c)) {
+        // In the order of the time they take: rows in turn, and 190 rows from
+        // one stripe's start to the next one's.
+        const int b = (int)(4.0f * __log2f(((float)n + 190.0f * (float)items) * (float)(64 * c) + 1.0f));
+        bucket = kBuckets - 1 - (b >= kBuckets ? kBuckets - 1 : b);
+        return 3;
+    }
     if (m > n || W > kBandMaxFrame) {
         if (m <= kBandMaxFrame) {
             const float work = (float)(n + 64) * (float)(128 * ((m + 127) / 128)) + 1.0f;
@@ -83,7 +92,7 @@ RA_DEV int band_classify(const PlanArgs &pa, int64_t p, int &bucket, float &scor
 // (score, end) is its result: a sentinel for invalid slices (NaN, -2) or the
 // value of a degenerate pair (empty query or empty region).  Returns -2 for
 // a global pair that the one-pair-per-lane kernel aligns (no output here).
-RA_DEV int classify(const PlanArgs &pa, int64_t p, int &bucket, float &score, int &end) {
+RA_DEV int classify(const PlanArgs &pa, int64_t p, float lim, int &bucket, float &score, int &end) {
     if (pa.paths) {
         int n = 0, s = 0, L = 0;
         if (path_interval(pa.path, p, n, s, L) != 0) return -2;   // the trace writes its sentinel
@@ -91,7 +100,7 @@ RA_DEV int classify(const PlanArgs &pa, int64_t p, int &bucket, float &score, in
         bucket = kBuckets - 1 - (b >= kBuckets ? kBuckets - 1 : b);
         return kRouteSingleLo;
     }
-    if (pa.band) return band_classify(pa, p, bucket, score, end);
+    if (pa.band) return band_classify(pa, p, lim, bucket, score, end);
     const PairArrays &a = pa.a;
     const int n = a.q_len[p];
     const int m = a.r_len[p];
@@ -172,8 +181,14 @@ RA_DEV double block_sum(double v) {
 
 // What a pair takes of its route's list: one entry, or its work items.
 RA_DEV int list_slots(const PlanArgs &pa, int64_t p, int route, float lim, int &k, int &c) {
-    if (!pa.chain || route != kRouteSingleLo) return 1;
+    if (!pa.chain || route != pa.chain_route) return 1;
     int items;
+    if (pa.band) {
+        const int m = pa.a.r_len[p], w = pa.band[p] < m - 1 ? pa.band[p] : m - 1;
+        k = 1;
+        (void)band_shape(pa.a.q_len[p], m, w, lim, items, c);
+        return items;
+    }
     if (pa.paths) {
         int n = 0, s = 0, L = 0;
         (void)path_interval(pa.path, p, n, s, L);
@@ -186,7 +201,7 @@ RA_DEV int list_slots(const PlanArgs &pa, int64_t p, int route, float lim, int &
 }
 
 RA_DEV void write_slots(const PlanArgs &pa, int64_t p, int route, int slots, int k, int c, int at) {
-    if (!pa.chain || route != kRouteSingleLo) {
+    if (!pa.chain || route != pa.chain_route) {
         pa.s.list[route * pa.s.capacity + at] = (int32_t)p;
         return;
     }
@@ -201,6 +216,13 @@ RA_DEV double plan_cells(const PlanArgs &pa, int64_t lo, int64_t hi) {
         for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
             int n = 0, s = 0, L = 0;
             if (path_interval(pa.path, p, n, s, L) == 0) cells += (double)n * (double)L;
+        }
+    } else if (pa.chain && pa.band) {   // the wider pairs are costed at the band's stripes
+        for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
+            const int n = pa.a.q_len[p], m = pa.a.r_len[p];
+            int c;
+            if (slices_ok(pa.a, p, false) && n > 0 && m > 0 && pa.band[p] >= 0)
+                cells += 64.0 * (double)band_cost(n, m, pa.band[p] < m - 1 ? pa.band[p] : m - 1, c);
         }
     } else if (pa.chain) {
         for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock)
@@ -227,7 +249,7 @@ RA_DEV void plan_count(const PlanArgs &pa, int64_t lo, int64_t hi, float lim, in
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
         int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
-        const int route = classify(pa, p, b, sc, e);
+        const int route = classify(pa, p, lim, b, sc, e);
         if (route >= 0) {
             atomicAdd(&h[route * kBuckets + b], list_slots(pa, p, route, lim, k, c));
         } else if (route == -1) {
@@ -242,7 +264,7 @@ RA_DEV void plan_scatter(const PlanArgs &pa, int64_t lo, int64_t hi, float lim, 
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
         int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
-        const int route = classify(pa, p, b, sc, e);
+        const int route = classify(pa, p, lim, b, sc, e);
         if (route >= 0) {
             const int bin = route * kBuckets + b;
             const int slots = list_slots(pa, p, route, lim, k, c);
@@ -272,7 +294,7 @@ RA_DEV void plan_scan(const PlanArgs &pa, int *hist) {
     if (lane == 63) {
         pa.s.counts[route] = run;
         pa.s.queue[route] = 0;
-        if (pa.chain && route == kRouteSingleLo) {
+        if (pa.chain && route == pa.chain_route) {
             *pa.sw.n_items = run < pa.sw.item_cap ? run : (int)pa.sw.item_cap;
             for (int x = 0; x < kQueues; ++x) pa.sw.queue[x * kQueueStride] = 0;
             *pa.sw.failed = 0;
@@ -336,7 +358,7 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_scatter(PlanArgs pa) {
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
         int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
-        const int route = classify(pa, p, b, sc, e);
+        const int route = classify(pa, p, lim, b, sc, e);
         if (route >= 0) atomicAdd(&cnt[route * kBuckets + b], list_slots(pa, p, route, lim, k, c));
     }
     __syncthreads();
@@ -398,6 +420,7 @@ hipError_t launch_plan(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cf
     pa.extend = a.rows != nullptr;
     pa.single_max = cfg.single_max;
     pa.chain = cfg.chain;
+    pa.chain_route = kRouteSingleLo;
     pa.lim_scale = kItemShare / (64.0f * (float)(cfg.sweep_grid > 0 ? cfg.sweep_grid : 1));
     pa.s = s;
     if (cfg.chain) pa.sw = *sw;
@@ -411,6 +434,7 @@ hipError_t launch_path_plan(const PathArgs &path, int grid, const PlanScratch &s
     pa.n_pairs = path.n_pairs;
     pa.buckets = kBuckets;
     pa.chain = 1;
+    pa.chain_route = kRouteSingleLo;
     pa.lim_scale = kItemShare / (64.0f * (float)grid);
     pa.s = s;
     pa.sw = sw;
@@ -420,7 +444,7 @@ hipError_t launch_path_plan(const PathArgs &path, int grid, const PlanScratch &s
 }
 
 hipError_t launch_band_plan(const PairArrays &a, const int32_t *band, int64_t n_pairs, const PlanScratch &s,
-                            hipStream_t stream) {
+                            const SweepScratch *sw, int grid, hipStream_t stream) {
     PlanArgs pa{};
     pa.a = a;
     pa.n_pairs = n_pairs;
@@ -428,6 +452,12 @@ hipError_t launch_band_plan(const PairArrays &a, const int32_t *band, int64_t n_
     pa.extend = 0;
     pa.s = s;
     pa.band = band;
+    if (sw) {
+        pa.chain = 1;
+        pa.chain_route = 3;
+        pa.sw = *sw;
+        pa.lim_scale = kItemShare / (64.0f * (float)grid);
+    }
     return run_plan(pa, stream);
 }
 

@@ -252,16 +252,18 @@ hipError_t launch_span_finish(const int32_t *end, const int32_t *rev_end, int64_
                               hipStream_t stream);
 // Banded subsequence DTW, one wave per pair.  The planner (same scratch and
 // kernels as the striped routes) gives every pair a band class (two frame
-// widths of the band-relative kernel, and the whole-region kernel for the
-// shapes it does not take) and writes the sentinels of the pairs that need
+// widths of the band-relative kernel, the whole-region kernel for the shapes
+// it does not take, and stripes for longer ones) and writes the sentinels of the pairs that need
 // no kernel; each class kernel then takes its list longest first from its
 // persistent queue.
 constexpr int kBandMaxFrame = 64 * 32;   // band columns one wave takes (C <= 32 per lane)
 constexpr int kBandLoMaxH = 4;           // class 0: frames of at most 4*128 columns (C <= 8)
+// sw (may be null): pairs that cost more than a wave's share of the call are
+// cut into items of the chained queue, on `grid` waves.
 hipError_t launch_band_plan(const PairArrays &a, const int32_t *band, int64_t n_pairs, const PlanScratch &s,
-                            hipStream_t stream);
+                            const SweepScratch *sw, int grid, hipStream_t stream);
 hipError_t launch_band(int cls, const PairArrays &a, const int32_t *band, int grid, const PlanScratch &s,
-                       hipStream_t stream);
+                       const SweepScratch *sw, hipStream_t stream);
 int band_blocks_per_cu(int cls);
 hipError_t launch_chain_sum(const float *gap_cost, int64_t n_gaps, const int64_t *chain_gap_off,
                             const int32_t *chain_gap_cnt, int64_t n_chains, float *out_chain_cost,

@@ -1001,11 +1001,24 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     DeviceInfo info;
     rc = device_info(dev, info);
     if (rc) return rc;
-    // Class 3 (striped band frames) gives each resident wave an edge slot.
-    const int grid3 = (int)std::min<int64_t>((int64_t)info.cus * ra::band_blocks_per_cu(3), n_pairs);
+    // Pairs that cost more than a wave's share are cut into stripes, at most
+    // one per 256 levels and at most `grid3` pairs of them (band_shape); class 3
+    // gives each resident wave an edge column.
+    const int64_t stripes = std::min<int64_t>(r_size, ra::kMaxRegion) / 256 + 1;
+    const int full3 = info.cus * ra::band_blocks_per_cu(3);
+    const int64_t item_cap = n_pairs + (full3 + 64) * stripes;
+    const int64_t ring = std::min<int64_t>(kMaxRing, 2 * (int64_t)full3);
+    const bool chain = item_cap < ((int64_t)1 << 28) && sweep_ready(dev, c.stream, item_cap, ring);
+    const int grid3 = (int)std::min<int64_t>(full3, chain ? n_pairs * stripes : n_pairs);
     StreamScratch *s = nullptr;
     rc = get_scratch(dev, c.stream, n_pairs, grid3, 0, false, true, s);
     if (rc) return rc;
+    ra::SweepScratch sw{};
+    if (chain) {
+        rc = get_sweep(*s, c.stream, item_cap, ring, sw);
+        if (rc) return rc;
+        sw.own = s->edge;
+    }
     ra::PairArrays a;
     a.q = q;
     a.q_size = q_size;
@@ -1024,17 +1037,23 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     a.bound = ra::kBoundSubseq;
     a.reverse = 0;
     const ra::PlanScratch ps = plan_view(*s);
-    hipError_t e = ra::launch_band_plan(a, band, n_pairs, ps, c.stream);
+    hipError_t e = ra::launch_band_plan(a, band, n_pairs, ps, chain ? &sw : nullptr, grid3, c.stream);
     if (e != hipSuccess) return hip_fail(e, "banded planning");
-    // The band classes run concurrently on the three internal streams (the
-    // two whole-region classes share one) joined back to the caller's stream.
+    // The band classes run concurrently: the cut pairs on the caller's stream,
+    // which needs no event to start after the plan, the frames and the whole
+    // regions on the internal ones, which it then waits for.  (Whole regions
+    // first, 128 registers a wave, held up the others: 3.9 ms against 3.4 on
+    // 40,000 chains.)
     if ((e = hipEventRecord(s->fork, c.stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     for (int i = 0; i < 3; ++i)
         if ((e = hipStreamWaitEvent(s->sub[i], s->fork, 0)) != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
-    for (int cls = 0; cls < ra::kNumBandClasses; ++cls) {
+    const int order[] = {3, 1, 0, 2};
+    const hipStream_t on[] = {s->sub[0], s->sub[1], s->sub[2], c.stream};
+    static_assert(ra::kNumBandClasses == 4, "a stream per class");
+    for (int cls : order) {
         const int grid = cls == 3 ? grid3
                                   : (int)std::min<int64_t>((int64_t)info.cus * ra::band_blocks_per_cu(cls), n_pairs);
-        e = ra::launch_band(cls, a, band, grid, ps, s->sub[cls < 3 ? cls : 2]);
+        e = ra::launch_band(cls, a, band, grid, ps, chain ? &sw : nullptr, on[cls]);
         if (e != hipSuccess) return hip_fail(e, "banded kernel");
     }
     for (int i = 0; i < 3; ++i) {
