@@ -154,6 +154,13 @@ RA_DEV int classify(const PlanArgs &pa, int64_t p, float lim, int &bucket, float
     return route;
 }
 
+// Pair p is on no list, as its width alone tells: a gap that the one-pair-per-lane
+// kernel aligns, or one that needs no kernel.  (Of a million gaps nearly all
+// are, and the scatter reads 4 bytes of each instead of 24, twice.)
+RA_DEV bool never_listed(const PlanArgs &pa, int64_t p) {
+    return !pa.paths && !pa.band && pa.a.bound == kBoundGlobal && !pa.a.reverse && pa.a.r_len[p] <= kTinyMaxCols;
+}
+
 // 1024 threads: each thread classifies a few pairs of a million-pair batch,
 // one after another; at 256 threads that chain of dependent loads set the
 // planning time.
@@ -262,6 +269,7 @@ RA_DEV void plan_count(const PlanArgs &pa, int64_t lo, int64_t hi, float lim, in
 // Writes the pairs [lo, hi) to their lists; next[bin] is the bin's cursor.
 RA_DEV void plan_scatter(const PlanArgs &pa, int64_t lo, int64_t hi, float lim, const int *base, int *next) {
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
+        if (never_listed(pa, p)) continue;
         int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
         const int route = classify(pa, p, lim, b, sc, e);
@@ -356,6 +364,7 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_scatter(PlanArgs pa) {
     int64_t lo, hi;
     plan_range(pa.n_pairs, lo, hi);
     for (int64_t p = lo + threadIdx.x; p < hi; p += kPlanBlock) {
+        if (never_listed(pa, p)) continue;
         int b = 0, e = 0, k = 0, c = 0;
         float sc = 0.0f;
         const int route = classify(pa, p, lim, b, sc, e);
@@ -399,7 +408,8 @@ static hipError_t run_plan(const PlanArgs &pa, hipStream_t stream) {
     const int64_t g64 = (n_pairs + kPlanBlock - 1) / kPlanBlock;
     const unsigned g = (unsigned)(g64 < kPlanGrid ? g64 : kPlanGrid);
     static_assert(kPlanGrid <= kPlanBlock && kBins <= kPlanBlock * (kPlanSmall / kPlanBlock), "start kernel covers both");
-    hipLaunchKernelGGL(k_plan_start, dim3(g), dim3(kPlanBlock), 0, stream, pa);
+    const unsigned g0 = pa.chain ? g : (kBins + kPlanBlock - 1) / kPlanBlock;   // without a queue it only clears the bins
+    hipLaunchKernelGGL(k_plan_start, dim3(g0), dim3(kPlanBlock), 0, stream, pa);
     hipLaunchKernelGGL(k_plan_count, dim3(g), dim3(kPlanBlock), 0, stream, pa);
     hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(64 * kNumRoutes), 0, stream, pa);
     hipLaunchKernelGGL(k_plan_scatter, dim3(g), dim3(kPlanBlock), 0, stream, pa);

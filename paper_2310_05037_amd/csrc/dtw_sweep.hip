@@ -239,9 +239,8 @@ void k_sweep(PairArrays a, SweepScratch sw) {
             // neighbour by about 96 steps instead of 160.
             it.block = n_items * 4 <= kLoneItems ? 16 : 32;
             it.corner = 0.0f;
-            ok = sweep_item<EXT>(x.c, pv, s0, s1 > s0 ? s1 : s0 + 1, it,
-                                       slot_of(sw, t - 1), slot_of(sw, t),
-                                       sw.own + (size_t)blockIdx.x * kOwnFloats, &wb, best, bj);
+            ok = sweep_item<EXT>(x.c, pv, s0, s1 > s0 ? s1 : s0 + 1, it, slot_of(sw, t - 1), slot_of(sw, t),
+                                 sw.own + (size_t)blockIdx.x * kOwnFloats, &wb, best, bj);
             // (every kEmpty is back: sweep_item waits for its stores)
             if (x.i > 0) slot_done(sw, t - 1);
         }
@@ -271,5 +270,9 @@ static int occupancy(K kernel) {
     return nb > 0 ? nb : 1;
 }
 
-int sweep_blocks_per_cu(bool extend) { return extend ? occupancy(k_sweep<true>) : occupancy(k_sweep<false>); }
+int sweep_blocks_per_cu(bool extend) {
+    static const int plain = occupancy(k_sweep<false>), ext = occupancy(k_sweep<true>);
+    return extend ? ext : plain;
+}
+
 }  // namespace ra
