@@ -18,6 +18,7 @@ struct PlanArgs {
     const int32_t *band;   // banded planning (band half-width per pair), else null
     int paths;             // planning of the direction pass (path), whose intervals are the regions
     PathArgs path;
+    int few;               // workgroups of the sweep for many long pairs (see plan_waves)
     int chain_route;       // the list whose counters the chained queue's items have
 };
 
@@ -304,6 +305,7 @@ RA_DEV void plan_scan(const PlanArgs &pa, int *hist) {
         pa.s.queue[route] = 0;
         if (pa.chain && route == pa.chain_route) {
             *pa.sw.n_items = run < pa.sw.item_cap ? run : (int)pa.sw.item_cap;
+            if (pa.sw.n_items[2] > run) pa.sw.n_items[2] = run;   // (no wave needs to ask for an item that is not there)
             for (int x = 0; x < kQueues; ++x) pa.sw.queue[x * kQueueStride] = 0;
             *pa.sw.failed = 0;
         }
@@ -332,6 +334,19 @@ RA_DEV float plan_lim_of_grid(const PlanArgs &pa) {
     return plan_lim(pa, block_sum(threadIdx.x < gridDim.x ? pa.sw.partial[threadIdx.x] : 0.0));
 }
 
+// Workgroups of the sweep that take items (streaming calls: all).  With four pairs or more for each and
+// a million cells a pair, 16 per CU: the sweep is bound by issue then, which
+// four waves per SIMD reach as five do, and the clock stays higher (100,000
+// uneven pairs 50.7 ms against 53.3).  Fewer pairs need the fifth to hide the
+// others' waits (10,000 pairs with starts 10.5 ms against 11.1, 1,024 long
+// regions 14.7 against 15.2), shorter ones to hide their starts and ends (20,785
+// pairs of 180 events 184 us against 197).
+RA_DEV void plan_waves(const PlanArgs &pa, float lim) {
+    const double cells = (double)lim / (double)pa.lim_scale;
+    const bool many = pa.few > 0 && pa.n_pairs >= 4 * (int64_t)pa.few && cells >= (double)(1 << 20) * (double)pa.n_pairs;
+    pa.sw.n_items[2] = many ? pa.few : 0x7fffffff;
+}
+
 // Each workgroup counts its pairs per (route, bucket) in LDS and adds the
 // non-zero bins to the global histogram: one global atomic per bin per
 // workgroup instead of one per pair.
@@ -339,6 +354,7 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_count(PlanArgs pa) {
     __shared__ int h[kBins];
     for (int i = threadIdx.x; i < kBins; i += kPlanBlock) h[i] = 0;
     const float lim = plan_lim_of_grid(pa);
+    if (pa.chain && blockIdx.x == 0 && threadIdx.x == 0) plan_waves(pa, lim);
     __syncthreads();
     int64_t lo, hi;
     plan_range(pa.n_pairs, lo, hi);
@@ -390,6 +406,7 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_small(PlanArgs pa) {
     if (pa.chain) {
         reset_ring(pa);
         lim = plan_lim(pa, plan_cells(pa, 0, pa.n_pairs));
+        if (threadIdx.x == 0) plan_waves(pa, lim);
     }
     __syncthreads();
     plan_count(pa, 0, pa.n_pairs, lim, h);
@@ -430,6 +447,7 @@ hipError_t launch_plan(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cf
     pa.extend = a.rows != nullptr;
     pa.single_max = cfg.single_max;
     pa.chain = cfg.chain;
+    pa.few = cfg.sweep_few;
     pa.chain_route = kRouteSingleLo;
     pa.lim_scale = kItemShare / (64.0f * (float)(cfg.sweep_grid > 0 ? cfg.sweep_grid : 1));
     pa.s = s;

@@ -94,7 +94,7 @@ constexpr int kQueueStride = 32;
 struct SweepScratch {
     uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
     int64_t item_cap;
-    int32_t *n_items;
+    int32_t *n_items;     // [3] items; failed; workgroups of the sweep that take items (at most the items)
     int32_t *queue;       // [kQueues * kQueueStride] work-queue heads
     float *ring;          // [ring_slots * kSlotFloats] edge columns between items
     float *own;           // [grid * kOwnFloats] edge columns within an item
@@ -210,6 +210,7 @@ struct LaunchCfg {
     bool persistent;    // atomic queue + LPT order (else static assignment, arrival order)
     bool chain;         // the stripe sweep takes every pair but over-long queries
     int sweep_grid;     // grid sizes (workgroups of one wave); waves of the sweep resident at once
+    int sweep_few;      // what of it large batches of long pairs take
     int lo_grid;
     int hi_grid;
     int multi_grid;     // also the number of edge slots

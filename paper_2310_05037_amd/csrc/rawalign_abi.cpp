@@ -429,7 +429,7 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     const int64_t full_stripes = c.n_pairs * ((levels + ra::kSweepStripe - 1) / ra::kSweepStripe + 1);
     cfg.chain = cfg.persistent && !tiny && !noalloc && !antidiag && full_stripes < ((int64_t)1 << 28);
     cfg.single_max = o.single_max ? o.single_max : ra::kSingleMaxRegion;
-    cfg.lo_grid = cfg.multi_grid = cfg.sweep_grid = 0;
+    cfg.lo_grid = cfg.multi_grid = cfg.sweep_grid = cfg.sweep_few = 0;
     int64_t ring = 0, item_cap = 0;
     if (cfg.chain) {
         // One kernel takes all three routes: the widest of their grids.
@@ -439,6 +439,7 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         const int64_t narrow = 64 * ra::kSweepMinC;
         cfg.sweep_grid = info.cus * (full ? occ : std::min(occ, std::max({w[0], w[1], w[2]})));
         cfg.sweep_grid = (int)std::min<int64_t>(cfg.sweep_grid, c.n_pairs * ((levels + narrow - 1) / narrow + 1));
+        cfg.sweep_few = full ? std::min(cfg.sweep_grid, 16 * info.cus) : cfg.sweep_grid;
         ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)cfg.sweep_grid));
         item_cap = full_stripes + 3 * (int64_t)cfg.sweep_grid;
         cfg.chain = sweep_ready(dev, c.stream, item_cap, ring);
