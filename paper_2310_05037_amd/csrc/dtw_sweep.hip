@@ -18,13 +18,13 @@
 // the chip, about 190 rows behind it, so a batch is spread over the chip
 // whether it has ten pairs or a hundred thousand: with one wave per pair a
 // batch took as long as its largest pair (start-of-alignment of 10,000 pairs:
-// 52 ms, now 10.5; 16 regions of 20,000 levels: 28 ms, now 14.5).  How the
+// 52 ms, now 10.5; 1,024 regions of 20,000 levels: 28, now 14.7).  How the
 // columns travel: dtw_chain.h.  An item that costs less than its share of the
 // batch takes all of its pair's stripes, edges through the wave's own column.
 //
 // What bounds it: instruction issue.  3.5 vector instructions per cell, a SIMD
-// issuing one in 2.2 cycles at most: 54 ms for 100,000 uneven pairs (1.08 T
-// cells, 20 T cells/s; 56 before), memory far from busy.  Few or short pairs
+// issuing one in 2.2 cycles at most: 50.9 ms for 100,000 uneven pairs (0.96 T
+// cells, 18.8 T cells/s; 55 before), memory far from busy.  Few or short pairs
 // wait for one wave's chain of dependent instructions instead.
 #include "dtw_chain.h"
 #include "dtw_rows.h"
