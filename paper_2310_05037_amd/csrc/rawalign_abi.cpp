@@ -476,8 +476,13 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         // One edge slot per resident multi-stripe wave.
         cfg.multi_grid = std::min(cfg.multi_grid, ra::kNoallocEdgeSlots);
     } else {
-        // Edge columns of the waves: the multi-stripe kernel's, or the sweep's own.
-        const int columns = !cfg.chain ? cfg.multi_grid : levels > ra::kSweepStripe ? cfg.sweep_grid : 0;
+        // Edge columns of the waves: the multi-stripe kernel's, or the sweep's own,
+        // and with it the former's too, which a captured call may have to take.
+        const int columns = !cfg.chain ? cfg.multi_grid
+                                       : std::max(levels > ra::kSweepStripe ? cfg.sweep_grid : 0,
+                                                  std::min(grid_of(info.cus, o.long_waves_per_cu,
+                                                                   ra::multi_blocks_per_cu(ext)),
+                                                           (int)std::min<int64_t>(c.n_pairs, 1 << 30)));
         rc = get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing, concurrent, s);
         if (rc) return rc;
         if (cfg.chain) {
