@@ -27,7 +27,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "internal.h"
+#include "dtw_shape.h"
 
 namespace ra {
 
@@ -361,31 +361,6 @@ RA_DEV void sweep(const PairView &pv, int col_base, float *edge, float corner, f
     }
     finish_lane<C, EXT>(pv, col0, A, best, bj);
     wave_min(best, bj);
-}
-
-// Work items of a pair in the stripe sweep: each sweeps k stripes of 64 c
-// columns one after another.  lim = 0: one item.  Else lim is what one item
-// may cost, in cells per lane (a share of the batch's cells per resident
-// wave): a longer one would end after the rest of the batch, so the pair is
-// cut into items of one stripe that run beside each other (an item of several
-// would hold up its right neighbour until its last).  Items narrower than 64
-// sqrt(26 m / n) columns, or 64 kSweepMinC, do not pay: each starts about 166
-// rows after its left neighbour, and a row of c columns costs a lone wave about
-// 52 + 5.2 c ns, so (n + 166 m / (64 c)) (52 + 5.2 c) is least there.
-RA_DEV void sweep_shape(int n, int m, float lim, int &items, int &k, int &c) {
-    const int stripes = m > kSweepStripe ? (m + kSweepStripe - 1) / kSweepStripe : 1;
-    items = 1;
-    if (lim > 0.0f) {
-        const float rows = (float)(n < 1 ? 1 : n), cols = (float)m;
-        const float want = ceilf(rows * cols / (64.0f * lim));
-        const float most = ceilf(cols / (64.0f * fmaxf((float)kSweepMinC, sqrtf(26.0f * cols / rows))));
-        const int more = (int)fminf(want, most);
-        if (want > 1.0f) items = more > stripes ? more : stripes;
-    }
-    k = items > 1 ? 1 : stripes;
-    c = (m + 64 * items * k - 1) / (64 * items * k);
-    if (c < 1) c = 1;
-    if (items > 1) items = (m + 64 * c - 1) / (64 * c);   // every item starts inside the region
 }
 
 // Stripe shape of a region of m levels: S stripes of 64*C columns,

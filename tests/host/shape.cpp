@@ -1,0 +1,12 @@
+// The planner's shape rules (csrc/dtw_shape.h) and limits, for the host tests.
+#include "dtw_shape.h"
+
+extern "C" {
+
+void sweep_shape(int n, int m, float lim, int *out) { ra::sweep_shape(n, m, lim, out[0], out[1], out[2]); }
+
+int limit(int which) {
+    const int v[] = {ra::kEdgeCap, ra::kSlotFloats, ra::kSweepStripe, ra::kSingleMaxRegion, ra::kMaxItems, ra::kSweepMaxC};
+    return v[which];
+}
+}
