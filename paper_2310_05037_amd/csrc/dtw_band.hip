@@ -663,7 +663,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_band_chain(PairArrays a, const int32_t *__restrict__ band, SweepScratch sw) {
     __shared__ __align__(16) BandBuf bb;
     const int n_items = *sw.n_items;
-    if ((int)blockIdx.x >= n_items) return;
+    if ((int)blockIdx.x >= sw.n_items[2]) return;
     float *own = sw.own + (size_t)blockIdx.x * kOwnFloats;
     for (int t = next_item(sw.queue); t < n_items; t = next_item(sw.queue)) {
         const ItemCode x = load_item(sw, t);

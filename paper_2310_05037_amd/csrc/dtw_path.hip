@@ -162,7 +162,7 @@ __global__ __launch_bounds__(64) void k_path_dirs(PathArgs pa, SweepScratch sw) 
         return;
     }
     const int n_items = *sw.n_items;
-    if ((int)blockIdx.x >= n_items) return;
+    if ((int)blockIdx.x >= sw.n_items[2]) return;
     for (int t = next_item(sw.queue); t < n_items; t = next_item(sw.queue)) {
         const ItemCode x = load_item(sw, t);
         bool ok = open_slots(sw, t, x);

@@ -305,7 +305,7 @@ RA_DEV void plan_scan(const PlanArgs &pa, int *hist) {
         pa.s.queue[route] = 0;
         if (pa.chain && route == pa.chain_route) {
             *pa.sw.n_items = run < pa.sw.item_cap ? run : (int)pa.sw.item_cap;
-            if (pa.sw.n_items[2] > run) pa.sw.n_items[2] = run;   // (no wave needs to ask for an item that is not there)
+            pa.sw.n_items[2] = live_workgroups(run, pa.sw.n_items[2]);   // (no others need to ask for items)
             for (int x = 0; x < kQueues; ++x) pa.sw.queue[x * kQueueStride] = 0;
             *pa.sw.failed = 0;
         }
@@ -343,7 +343,7 @@ RA_DEV float plan_lim_of_grid(const PlanArgs &pa) {
 // pairs of 180 events 184 us against 197).
 RA_DEV void plan_waves(const PlanArgs &pa, float lim) {
     const double cells = (double)lim / (double)pa.lim_scale;
-    const bool many = pa.few > 0 && pa.n_pairs >= 4 * (int64_t)pa.few && cells >= (double)(1 << 20) * (double)pa.n_pairs;
+    const bool many = pa.few > 0 && !pa.extend && pa.n_pairs >= 4 * (int64_t)pa.few && cells >= (double)(1 << 20) * (double)pa.n_pairs;
     pa.sw.n_items[2] = many ? pa.few : 0x7fffffff;
 }
 

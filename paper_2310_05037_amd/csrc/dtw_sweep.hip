@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSweepWaves,
 void k_sweep(PairArrays a, SweepScratch sw) {
     __shared__ __align__(16) WaveBuf wb;
     const int n_items = *sw.n_items;
-    if ((int)blockIdx.x >= (EXT ? n_items : sw.n_items[2])) return;   // more waves than are of use
+    if ((int)blockIdx.x >= sw.n_items[2]) return;   // more waves than are of use
     for (int t = next_item(sw.queue); t < n_items; t = next_item(sw.queue)) {
         const ItemCode x = load_item(sw, t);
         const bool last = x.i + 1 == x.items;

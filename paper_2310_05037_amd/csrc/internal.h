@@ -90,11 +90,29 @@ static_assert(kSweepMaxC < 64 && kMaxItems < 512 && kMaxRegion / kSweepStripe < 
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 32;
 
+// Workgroup b's queue.  A wave may wait for the item before its own, which is in
+// another queue, so a launch that has slots at all needs a wave on every queue.
+// Workgroups go round the dies in turn and each die starts its own in order.
+// In the first 64 each row of eight is turned by one against the row before, so
+// the first eight on any die cover every queue (as do the first eight of all,
+// where the chip is one die).  With b mod kQueues throughout, a queue's
+// workgroups were all on one die, and two launches on different streams that
+// each held some dies waited for each other.  A launch is held up only where no
+// die has eight slots for it, and then the others' waves there are of launches
+// that do.  (Turned throughout: 4,096 pairs 798 us for 771, 500 paths 6.3 ms for 6.0.)
+constexpr int kDies = 8;
+constexpr int kCover = kDies * kQueues;   // workgroups every launch has
+RA_HOST_DEV constexpr int queue_of(int b, int queues) { return (b < kCover ? b + b / kDies : b) % queues; }
+// Workgroups that take items: one for each, at most `most`, and the covering ones.
+RA_HOST_DEV constexpr int live_workgroups(int n_items, int most) {
+    return n_items < kCover || most < kCover ? kCover : n_items < most ? n_items : most;
+}
+
 // Scratch of the chained sweep.
 struct SweepScratch {
     uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
     int64_t item_cap;
-    int32_t *n_items;     // [3] items; failed; workgroups of the sweep that take items (at most the items)
+    int32_t *n_items;     // [3] items; failed; workgroups that take items (live_workgroups)
     int32_t *queue;       // [kQueues * kQueueStride] work-queue heads
     float *ring;          // [ring_slots * kSlotFloats] edge columns between items
     float *own;           // [grid * kOwnFloats] edge columns within an item

@@ -381,6 +381,12 @@ int check_call(const Call &c) {
     return RAWALIGN_OK;
 }
 
+// Workgroups of a chained launch: no more than it can have items, but a wave
+// for every queue on whichever die it starts (ra::queue_of).
+int chain_grid(int resident, int64_t items) {
+    return (int)std::max<int64_t>(ra::kCover, std::min<int64_t>(resident, items));
+}
+
 int grid_of(int cus, int per_cu_opt, int occupancy) { return cus * (per_cu_opt ? per_cu_opt : occupancy); }
 
 static_assert(RAWALIGN_NOALLOC_MAX_PAIRS == ra::kNoallocMaxPairs, "allocation-free pair limit");
@@ -438,7 +444,7 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         const bool full = !w[0] || !w[1] || !w[2];
         const int64_t narrow = 64 * ra::kSweepMinC;
         cfg.sweep_grid = info.cus * (full ? occ : std::min(occ, std::max({w[0], w[1], w[2]})));
-        cfg.sweep_grid = (int)std::min<int64_t>(cfg.sweep_grid, c.n_pairs * ((levels + narrow - 1) / narrow + 1));
+        cfg.sweep_grid = chain_grid(cfg.sweep_grid, c.n_pairs * ((levels + narrow - 1) / narrow + 1));
         cfg.sweep_few = full ? std::min(cfg.sweep_grid, 16 * info.cus) : cfg.sweep_grid;
         ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)cfg.sweep_grid));
         item_cap = full_stripes + 3 * (int64_t)cfg.sweep_grid;
@@ -972,7 +978,7 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
     // Items: one per pair, one per 2,048 columns and what the planner's share
     // adds (path_shape: c is at most twice the least).
     const int64_t levels = std::min<int64_t>(r_size, ra::kMaxRegion);
-    const int grid = (int)std::min<int64_t>((int64_t)info.cus * ra::path_blocks_per_cu(), n_pairs * (levels / 256 + 1));
+    const int grid = chain_grid(info.cus * ra::path_blocks_per_cu(), n_pairs * (levels / 256 + 1));
     const int64_t item_cap = n_pairs * (levels / ra::kSweepStripe + 2) + 3 * (int64_t)grid;
     const int64_t ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)grid));
     ra::SweepScratch sw{};
@@ -1015,7 +1021,7 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     const int64_t item_cap = n_pairs + (full3 + 64) * stripes;
     const int64_t ring = std::min<int64_t>(kMaxRing, 2 * (int64_t)full3);
     const bool chain = item_cap < ((int64_t)1 << 28) && sweep_ready(dev, c.stream, item_cap, ring);
-    const int grid3 = (int)std::min<int64_t>(full3, chain ? n_pairs * stripes : n_pairs);
+    const int grid3 = chain ? chain_grid(full3, n_pairs * stripes) : (int)std::min<int64_t>(full3, n_pairs);
     StreamScratch *s = nullptr;
     rc = get_scratch(dev, c.stream, n_pairs, grid3, 0, false, true, s);
     if (rc) return rc;
