@@ -249,6 +249,8 @@ int rawalign_decide(const float *score, int64_t n_pairs, const int64_t *cand_off
  *     computation; completed pairs' out_score/out_end equal
  *     rawalign_dtw_batch's bit for bit.  Which pairs are dropped is not
  *     specified.
+ *   - A pair one of whose rounds was given up (see rawalign_dtw_batch) ends
+ *     with NaN, -5 and is no candidate any more, as in rawalign_decide.
  *   - max_query: the longest q_len the caller passes; longer pairs get the
  *     sentinel NaN, -2.  block_rows in [64, RAWALIGN_MAX_QUERY_LONG].  A
  *     pair claimed by several reads, or by none, is aligned whole.  rows must

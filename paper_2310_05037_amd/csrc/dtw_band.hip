@@ -655,7 +655,7 @@ RA_DEV BandView band_view(const PairArrays &a, const int32_t *band, int p) {
 RA_DEV void band_result(const PairArrays &a, int p, float best, int bj) {
     if (__lane_id() == 0) {
         a.out_score[p] = best;
-        a.out_end[p] = best < kInf || bj == -5 ? bj : -1;
+        a.out_end[p] = best < kInf || bj == kGaveUp ? bj : -1;
     }
 }
 
@@ -679,7 +679,7 @@ void k_band_chain(PairArrays a, const int32_t *__restrict__ band, SweepScratch s
         if (x.i + 1 == x.items) {
             if (!ok || (x.items > 1 && gave_up(sw))) {
                 best = __builtin_nanf("");
-                bj = -5;
+                bj = kGaveUp;
             }
             band_result(a, x.p, best, bj);
         }

@@ -24,20 +24,10 @@
 // A persistent kernel with one wave per pair, which did all of this in one
 // launch, took as long as its largest first candidate: 31 ms for 20,000 pairs
 // of the uneven batch.
+#include "dtw_bnb.h"
 #include "dtw_device.h"
 
 namespace ra {
-
-// Monotone encoding of doubles as unsigned 64-bit keys (larger double ->
-// larger key), so the per-read best can be raised with an integer atomicMax.
-RA_DEV uint64_t order_key(double d) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, d);
-    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-}
-RA_DEV double order_value(uint64_t k) {
-    const uint64_t b = (k >> 63) ? (k & 0x7fffffffffffffffull) : ~k;
-    return __builtin_bit_cast(double, b);
-}
 
 // Pair checks: the same rules as the batch entry point (slices inside q and
 // r, region and query limits) plus the row slot and the caller's longest
@@ -77,14 +67,6 @@ __global__ void k_bnb_claim(BnbArgs b) {
     b.s.status[p0] = kBnbFirst;
 }
 
-// The next round's part of pair p: rows [from, to), or none (from < 0).
-RA_DEV void bnb_part(const BnbArgs &b, int64_t p, int from, int to) {
-    b.s.part_off[p] = b.a.q_off[p] + (from < 0 ? 0 : from);
-    b.s.part_len[p] = from < 0 ? -1 : to - from;   // a negative length is skipped
-    b.s.part_first[p] = from == 0;
-    b.s.part_row[p] = from;
-}
-
 // Round 0, and the results of pairs that need no DTW.
 __global__ void k_bnb_start(BnbArgs b, int block_rows) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -109,49 +91,17 @@ __global__ void k_bnb_start(BnbArgs b, int block_rows) {
     bnb_part(b, p, settled ? -1 : 0, whole ? a.q_len[p] : block_rows);
 }
 
-// After a round: results of the pairs it completed, which raise their reads'
-// best.
 __global__ void k_bnb_finish(BnbArgs b) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= b.n_pairs || b.s.status[p] == kBnbDone || b.s.part_row[p] < 0) return;
-    if (b.s.part_row[p] + b.s.part_len[p] < b.a.q_len[p]) return;
-    const float cost = b.s.part_score[p];
-    b.a.out_score[p] = cost;
-    b.a.out_end[p] = b.s.part_end[p];
-    b.s.status[p] = kBnbDone;
-    const int k = b.s.read_of[p];
-    if (k >= 0)
-        atomicMax((unsigned long long *)&b.s.best[k],
-                  (unsigned long long)order_key(b.b_match * (double)b.n_events[k] - (double)cost));
+    if (p >= b.n_pairs) return;
+    uint64_t key;
+    const int k = bnb_finish(b, p, key);
+    if (k >= 0) atomicMax((unsigned long long *)&b.s.best[k], (unsigned long long)key);
 }
 
-// The open pairs' next round (every pair here has one read: the others were
-// aligned whole), or their end.  A pair is dropped in the row where its
-// minimum reaches `need`; at min / rows a row that is need / min times the rows
-// so far, and 5 % are added for rows that cost less.  Steps of a fixed length
-// or ratio instead sweep a pair up to half further and take more rounds, each
-// 63 steps of skew per pair and 45 us of launches: 11.8 ms against 7.8 on 20,000
-// pairs of the uneven batch (82 % of them dropped).
 __global__ void k_bnb_advance(BnbArgs b, int block_rows, bool whole) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= b.n_pairs) return;
-    if (b.s.status[p] == kBnbDone) {
-        bnb_part(b, p, -1, 0);
-        return;
-    }
-    const int k = b.s.read_of[p];
-    const double most = b.b_match * (double)b.n_events[k], best = order_value(b.s.best[k]);
-    const double cost = b.s.part_score[p];
-    if (most - cost < best) {
-        b.a.out_score[p] = kInf;   // cannot win: treated as unmapped by the decision
-        b.a.out_end[p] = -3;
-        b.s.status[p] = kBnbDone;
-        bnb_part(b, p, -1, 0);
-        return;
-    }
-    const int n = b.a.q_len[p], from = b.s.part_row[p] + b.s.part_len[p], least = block_rows / 4;
-    const double to = fmax(1.05 * (double)from * ((most - best) / cost), (double)from) + (double)least;
-    bnb_part(b, p, from, !whole && to < (double)(n - least) ? (int)to : n);
+    if (p < b.n_pairs) bnb_advance(b, p, block_rows, whole);
 }
 
 static unsigned grid_of(int64_t n) { return (unsigned)((n + 255) / 256); }

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64) void k_path_trace(PathArgs pa, const int32_t *f
     for (int64_t p = blockIdx.x; p < pa.n_pairs; p += gridDim.x) {
         int n = 0, s = 0, L = 0;
         int st = path_interval(pa, p, n, s, L);
-        if (st == 0 && failed && *failed) st = -5;   // a wait of the direction pass was given up
+        if (st == 0 && failed && *failed) st = kGaveUp;   // a wait of the direction pass was given up
         st = __builtin_amdgcn_readfirstlane(st);
         s = __builtin_amdgcn_readfirstlane(s);
         const int64_t off = pa.path_off[p];

@@ -248,7 +248,7 @@ void k_sweep(PairArrays a, SweepScratch sw) {
         if (last) {
             if (!ok || (x.items > 1 && gave_up(sw))) {
                 best = __builtin_nanf("");
-                bj = -5;
+                bj = kGaveUp;
             }
             write_result(a, x.p, best, bj);
         }

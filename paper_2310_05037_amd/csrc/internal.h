@@ -108,6 +108,9 @@ RA_HOST_DEV constexpr int live_workgroups(int n_items, int most) {
     return n_items < kCover || most < kCover ? kCover : n_items < most ? n_items : most;
 }
 
+// End (with a NaN score) of a cut pair one of whose waits was given up.
+constexpr int kGaveUp = -5;
+
 // Scratch of the chained sweep.
 struct SweepScratch {
     uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
