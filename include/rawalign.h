@@ -284,8 +284,9 @@ int rawalign_map_bnb(const float *q, int64_t q_size, const int64_t *q_off, const
  * interval [start, end] aligned globally costs C_DTW.
  *   Arguments as in rawalign_dtw_batch_ex, plus out_start (device, int32 per
  *   pair).  Pairs without an end keep its sentinel as their start (-1
- *   degenerate, -2 invalid).  opts: as in rawalign_dtw_batch_ex (NULL = tuned
- *   or defaults) for both passes; long_kernel must be RAWALIGN_LONG_STRIPED.
+ *   degenerate, -2 invalid, -5 given up); a pair whose reverse pass was given
+ *   up (see rawalign_dtw_batch) keeps its score and end and has start -5.
+ *   opts: as in rawalign_dtw_batch_ex (NULL = tuned or defaults) for both passes; long_kernel must be RAWALIGN_LONG_STRIPED.
  *   Scratch: that of rawalign_dtw_batch plus 12 bytes per pair, per (device,
  *   stream).  The reverse pass sweeps sum(e + 1) * n cells.
  */
@@ -325,7 +326,7 @@ int rawalign_dtw_span(const float *q, int64_t q_size, const int64_t *q_off, cons
  *   opts->flags & RAWALIGN_FLAG_SPAN_GIVEN: out_score, out_end and
  *   out_start are inputs, the result of rawalign_dtw_span on the same pairs
  *   (an end or start that no alignment of the pair can have gets -2 in
- *   every entry); the span passes are skipped.
+ *   every entry, -5 gets -5); the span passes are skipped.
  *   Other arguments, opts, errors and scratch as in rawalign_dtw_span.  The
  *   directions are recorded stripe by stripe, the stripes of a long interval by
  *   several waves at once (in a stream capture before that call's scratch is

@@ -54,13 +54,14 @@ hipError_t launch_path(const PathArgs &pa, int grid, const SweepScratch &sw, hip
 int path_blocks_per_cu();
 
 // Interval of pair p, or a sentinel: -1 / -2 from the start pass (empty
-// query or region / invalid slice), -4 when the pair's workspace range is
-// missing or too small.
-__device__ __forceinline__ int path_interval(const PathArgs &pa, int64_t p, int &n, int &s, int &L) {
+// query or region / invalid slice), kGaveUp where one of its passes was given
+// up, -4 when the pair's workspace range is missing or too small.
+__host__ __device__ __forceinline__ int path_interval(const PathArgs &pa, int64_t p, int &n, int &s, int &L) {
     n = pa.q_len[p];
     const int e = pa.end[p];
     s = pa.start[p];
     if (e < 0) return e;
+    if (s == kGaveUp) return s;
     const int m = pa.r_len[p];
     const int64_t qo = pa.q_off[p], ro = pa.r_off[p];
     if (n < 1 || s < 0 || s > e || e >= m || qo < 0 || ro < 0 || qo + n > pa.q_size || ro + m > pa.r_size)
@@ -74,7 +75,7 @@ __device__ __forceinline__ int path_interval(const PathArgs &pa, int64_t p, int 
 // Work items of a pair's n x L direction table: one per stripe of 64 c columns,
 // c = 4, 8, 16 or 32, where the pair costs more than lim (see sweep_shape);
 // else, and where a ring slot or an item's fields are too small, one for all.
-__device__ __forceinline__ void path_shape(int n, int L, float lim, int &items, int &c) {
+__host__ __device__ __forceinline__ void path_shape(int n, int L, float lim, int &items, int &c) {
     const float cost = (float)n * (float)L / 64.0f;
     const bool split = n <= kEdgeCap && L <= kMaxRegion && cost > lim;
     const int want = split ? (int)fminf(ceilf(cost / lim), 1024.0f) : 1;

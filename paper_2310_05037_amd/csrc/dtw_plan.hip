@@ -498,13 +498,11 @@ __global__ void k_span_prep(const int32_t *__restrict__ end, int64_t n_pairs, in
     if (p < n_pairs) rev_len[p] = end[p] >= 0 ? end[p] + 1 : 0;
 }
 
-// Its best end k (smallest on ties) is the forward column end - k: the
-// latest start among the optimal paths ending at end.  Pairs without an
-// end keep their sentinel (-1 degenerate, -2 invalid).
+// Starts from the reverse pass's best ends (smallest on ties).
 __global__ void k_span_finish(const int32_t *__restrict__ end, const int32_t *__restrict__ rev_end, int64_t n_pairs,
                               int32_t *__restrict__ out_start) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < n_pairs) out_start[p] = end[p] >= 0 ? end[p] - rev_end[p] : end[p];
+    if (p < n_pairs) out_start[p] = span_start(end[p], rev_end[p]);
 }
 
 hipError_t launch_span_prep(const int32_t *end, int64_t n_pairs, int32_t *rev_len, hipStream_t stream) {

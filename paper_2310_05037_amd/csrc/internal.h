@@ -111,6 +111,14 @@ RA_HOST_DEV constexpr int live_workgroups(int n_items, int most) {
 // End (with a NaN score) of a cut pair one of whose waits was given up.
 constexpr int kGaveUp = -5;
 
+// Start of an alignment from its end and the reverse pass's best end k: the
+// forward column end - k, the latest start among the optimal paths ending at end.
+// Pairs without an end keep their sentinel (-1 degenerate, -2 invalid), pairs
+// whose reverse pass was given up have no start.
+RA_HOST_DEV constexpr int span_start(int end, int rev_end) {
+    return end < 0 ? end : rev_end == kGaveUp ? kGaveUp : end - rev_end;
+}
+
 // Scratch of the chained sweep.
 struct SweepScratch {
     uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
