@@ -332,7 +332,7 @@ int rawalign_dtw_span(const float *q, int64_t q_size, const int64_t *q_off, cons
  *   several waves at once (in a stream capture before that call's scratch is
  *   there, by one wave per pair, without scratch), and one wave per pair then
  *   follows them back.  A sweep given up (see rawalign_dtw_batch) gives -5 in
- *   every entry.
+ *   every entry of the pairs it cut.
  */
 int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, const int32_t *q_len,
                       const float *r, int64_t r_size, const int64_t *r_off, const int32_t *r_len,

@@ -14,8 +14,8 @@
 // wave (queue_of), so the lowest unfinished item is taken, never waits and the
 // list drains.  A
 // wait is nevertheless capped (kSpinTicks); past the cap every wave stops
-// waiting, the pairs left are marked as failed and the ring is refilled by the
-// next call's planner.
+// waiting, the cut pairs left are marked as failed and the ring is refilled by
+// the next call's planner.
 #pragma once
 
 #include "dtw_device.h"
@@ -114,12 +114,13 @@ RA_DEV ItemCode load_item(const SweepScratch &sw, int t) {
 
 // Neither item t's slot nor the one it reads (item i of its pair, i > 0) holds
 // anything of their earlier items: an early reader would take their values.  A
-// pair's last item, which stores nothing, passes its slot on at once.
+// pair's last item, which stores nothing, passes its slot on at once.  False
+// when given up, except for a pair that is not cut: it uses no slot.
 RA_DEV bool open_slots(const SweepScratch &sw, int t, const ItemCode &x) {
     bool ok = slot_free(sw, t);
     if (x.i > 0 && ok) ok = slot_free(sw, t - 1);
     if (x.i + 1 == x.items) slot_done(sw, t);
-    return ok;
+    return ok || x.items == 1;
 }
 
 RA_DEV float *slot_of(const SweepScratch &sw, int t) {   // t >= -1

@@ -84,6 +84,13 @@ __host__ __device__ __forceinline__ void path_shape(int n, int L, float lim, int
     c = least <= 4 ? 4 : least <= 8 ? 8 : least <= 16 ? 16 : 32;
     items = split ? (L + 64 * c - 1) / (64 * c) : 1;
 }
+// A wait of the direction pass was given up (`failed`) and the pair is one of
+// those that were cut: its table is in doubt.
+__host__ __device__ __forceinline__ bool path_lost(int n, int L, float lim, bool failed) {
+    int items = 1, c;
+    if (failed) path_shape(n, L, lim, items, c);
+    return items > 1;
+}
 static_assert(kMaxRegion / (64 * 4) < 512, "item fields");
 
 }  // namespace ra

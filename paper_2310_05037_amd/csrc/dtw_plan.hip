@@ -345,6 +345,7 @@ RA_DEV void plan_waves(const PlanArgs &pa, float lim) {
     const double cells = (double)lim / (double)pa.lim_scale;
     const bool many = pa.few > 0 && !pa.extend && pa.n_pairs >= 4 * (int64_t)pa.few && cells >= (double)(1 << 20) * (double)pa.n_pairs;
     pa.sw.n_items[2] = many ? pa.few : 0x7fffffff;
+    pa.sw.n_items[3] = __builtin_bit_cast(int, lim);   // (the trace of paths asks which were cut)
 }
 
 // Each workgroup counts its pairs per (route, bucket) in LDS and adds the

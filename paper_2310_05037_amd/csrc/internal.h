@@ -123,7 +123,7 @@ RA_HOST_DEV constexpr int span_start(int end, int rev_end) {
 struct SweepScratch {
     uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
     int64_t item_cap;
-    int32_t *n_items;     // [3] items; failed; workgroups that take items (live_workgroups)
+    int32_t *n_items;     // [4] items; failed; workgroups that take items (live_workgroups); the share (float bits)
     int32_t *queue;       // [kQueues * kQueueStride] work-queue heads
     float *ring;          // [ring_slots * kSlotFloats] edge columns between items
     float *own;           // [grid * kOwnFloats] edge columns within an item
