@@ -129,8 +129,9 @@ int rawalign_opts_default(rawalign_opts *opts);
  * captured before the sweep's own scratch is there, a call takes the kernels
  * of plain mode's routes in persistent queues instead.  A sweep whose waves
  * wait for each other longer than 5 s (a GPU that does not run them) ends with
- * NaN and end -5 for the pairs it cut.
+ * NaN and end RAWALIGN_END_GIVEN_UP for the pairs it cut.
  */
+#define RAWALIGN_END_GIVEN_UP (-5)
 int rawalign_dtw_batch(const float *q, int64_t q_size, const int64_t *q_off, const int32_t *q_len,
                        const float *r, int64_t r_size, const int64_t *r_off, const int32_t *r_len,
                        int64_t n_pairs, float *out_score, int32_t *out_end, void *stream);
@@ -197,7 +198,10 @@ int rawalign_dtw_batch_noalloc(const float *q, int64_t q_size, const int64_t *q_
  *   n_jobs, out_score, out_end, stream  as above
  * Jobs must not share a row.  A job whose row slice leaves [0, rows_size)
  * gets score NaN, end -2 and its row is untouched.  q_len == 0 leaves the
- * row unchanged and reports the stored row's minimum.
+ * row unchanged and reports the stored row's minimum.  A job given up (score
+ * NaN, end -5, see rawalign_dtw_batch) may have written part of its row, which
+ * then belongs to no prefix: align all events so far again, with first_chunk
+ * set, or drop the read.
  */
 int rawalign_dtw_extend(const float *q, int64_t q_size, const int64_t *q_off, const int32_t *q_len,
                         const float *r, int64_t r_size, const int64_t *r_off, const int32_t *r_len,

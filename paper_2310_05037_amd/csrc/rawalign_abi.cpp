@@ -389,6 +389,7 @@ int chain_grid(int resident, int64_t items) {
 
 int grid_of(int cus, int per_cu_opt, int occupancy) { return cus * (per_cu_opt ? per_cu_opt : occupancy); }
 
+static_assert(RAWALIGN_END_GIVEN_UP == ra::kGaveUp, "end of a pair given up");
 static_assert(RAWALIGN_NOALLOC_MAX_PAIRS == ra::kNoallocMaxPairs, "allocation-free pair limit");
 static_assert(RAWALIGN_NOALLOC_EDGE_SLOTS == ra::kNoallocEdgeSlots, "allocation-free edge slots");
 static_assert(RAWALIGN_NOALLOC_SCRATCH_BYTES == ra::kNoallocScratchBytes, "allocation-free scratch size");

@@ -25,6 +25,7 @@ RAWALIGN_MAX_REGION = 65536
 RAWALIGN_MAX_QUERY_LONG = 16384
 RAWALIGN_NOALLOC_MAX_PAIRS = 131072
 RAWALIGN_NOALLOC_EDGE_SLOTS = 512
+RAWALIGN_END_GIVEN_UP = -5
 MODE_PLAIN = 0
 MODE_PERSISTENT = 1
 LONG_STRIPED = 0

@@ -16,6 +16,8 @@ Engine (host logic only):
     (one job per candidate) and runs the extend and decision kernels once;
   * a read finishes when it maps or after its last chunk; its rows are
     freed and waiting reads may be admitted;
+  * a read one of whose jobs the library gave up fails: its resident row is
+    not the alignment's any more;
   * per chunk it records the latency from the moment the chunk became
     available to the moment its decision is on the host.
 Backends: GpuBackend (librawalign, optionally replaying one captured HIP
@@ -32,6 +34,8 @@ import time
 from dataclasses import dataclass, field
 
 import numpy as np
+
+from .lib import RAWALIGN_END_GIVEN_UP
 
 B_MATCH = 0.4
 SCORE_THRESHOLD = 20.0
@@ -284,6 +288,10 @@ class Engine:
         self.cells += b.cells
         for t, st in enumerate(b.reads):
             lo, k = int(b.cand_off[t]), int(b.cand_cnt[t])
+            if (end[lo:lo + k] == RAWALIGN_END_GIVEN_UP).any():
+                if not st.done:
+                    self._finish(st, "failed")
+                continue
             c = st.next_chunk
             st.results.append((int(best[t]) - lo if best[t] >= 0 else -1, float(best_score[t]), int(mapped[t]),
                                score[lo:lo + k].copy(), end[lo:lo + k].copy()))
