@@ -245,21 +245,22 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
     return RAWALIGN_OK;
 }
 
-// The sweep's scratch can be had: it is there, or the stream is not being
-// captured.  A captured call that would have to allocate it takes the routes
-// that need none.
-bool sweep_ready(int dev, hipStream_t stream, int64_t item_cap, int64_t ring_slots) {
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        const StreamScratch &s = g_scratch[{dev, stream}];
-        if (s.item_cap >= item_cap && s.ring_slots >= ring_slots) return true;
-    }
+bool is_capturing(hipStream_t stream) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
         (void)hipGetLastError();
-        return true;
+        return false;
     }
-    return st == hipStreamCaptureStatusNone;
+    return st != hipStreamCaptureStatusNone;
+}
+
+// All that a chained call needs is there: its work items, ring slots and edge
+// columns.  A captured call, which may not allocate, takes the routes that need
+// none of them otherwise.
+bool sweep_there(int dev, hipStream_t stream, int64_t item_cap, int64_t ring_slots, int64_t columns) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    const StreamScratch &s = g_scratch[{dev, stream}];
+    return s.item_cap >= item_cap && s.ring_slots >= ring_slots && s.edge_slots >= columns;
 }
 
 // Planning scratch of the one-pair-per-lane kernel (global calls only).
@@ -437,7 +438,8 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     cfg.chain = cfg.persistent && !tiny && !noalloc && !antidiag && full_stripes < ((int64_t)1 << 28);
     cfg.single_max = o.single_max ? o.single_max : ra::kSingleMaxRegion;
     cfg.lo_grid = cfg.multi_grid = cfg.sweep_grid = cfg.sweep_few = 0;
-    int64_t ring = 0, item_cap = 0;
+    const bool capture = !noalloc && is_capturing(c.stream);
+    int64_t ring = 0, item_cap = 0, own = 0;
     if (cfg.chain) {
         // One kernel takes all three routes: the widest of their grids.
         const int occ = ra::sweep_blocks_per_cu(ext);
@@ -449,7 +451,8 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         cfg.sweep_few = full ? std::min(cfg.sweep_grid, 16 * info.cus) : cfg.sweep_grid;
         ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)cfg.sweep_grid));
         item_cap = full_stripes + 3 * (int64_t)cfg.sweep_grid;
-        cfg.chain = sweep_ready(dev, c.stream, item_cap, ring);
+        own = levels > ra::kSweepStripe ? cfg.sweep_grid : 0;
+        cfg.chain = !capture || sweep_there(dev, c.stream, item_cap, ring, own);
     }
     if (!cfg.chain) {
         cfg.lo_grid = grid_of(info.cus, o.lo_waves_per_cu, ra::single_lo_blocks_per_cu(ext));
@@ -483,14 +486,16 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         // One edge slot per resident multi-stripe wave.
         cfg.multi_grid = std::min(cfg.multi_grid, ra::kNoallocEdgeSlots);
     } else {
-        // Edge columns of the waves: the multi-stripe kernel's, or the sweep's own,
-        // and with it the former's too, which a captured call may have to take.
-        const int columns = !cfg.chain ? cfg.multi_grid
-                                       : std::max(levels > ra::kSweepStripe ? cfg.sweep_grid : 0,
-                                                  std::min(grid_of(info.cus, o.long_waves_per_cu,
-                                                                   ra::multi_blocks_per_cu(ext)),
-                                                           (int)std::min<int64_t>(c.n_pairs, 1 << 30)));
-        rc = get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing, concurrent, s);
+        // Edge columns of the waves: the multi-stripe kernel's, or the sweep's own.
+        // A call that may allocate also gets what a captured call of no more
+        // pairs needs if it cannot have the sweep's: the former's, and the
+        // internal streams.
+        int64_t columns = cfg.chain ? own : cfg.multi_grid;
+        if (cfg.chain && !capture)
+            columns = std::max<int64_t>(own, std::min<int64_t>(grid_of(info.cus, o.long_waves_per_cu,
+                                                                       ra::multi_blocks_per_cu(ext)), c.n_pairs));
+        rc = get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing,
+                         capture ? concurrent : o.streams == 3, s);
         if (rc) return rc;
         if (cfg.chain) {
             rc = get_sweep(*s, c.stream, item_cap, ring, sw);
@@ -985,7 +990,7 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
     ra::SweepScratch sw{};
     // Past the queue's range, and in a capture before the scratch is there, one
     // wave per pair.
-    if (item_cap >= ((int64_t)1 << 28) || !sweep_ready(dev, st, item_cap, ring)) {
+    if (item_cap >= ((int64_t)1 << 28) || (is_capturing(st) && !sweep_there(dev, st, item_cap, ring, 0))) {
         const hipError_t e = ra::launch_path(pa, (int)n_pairs, sw, st);
         return e == hipSuccess ? RAWALIGN_OK : hip_fail(e, "path kernels");
     }
@@ -1021,8 +1026,10 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     const int full3 = info.cus * ra::band_blocks_per_cu(3);
     const int64_t item_cap = n_pairs + (full3 + 64) * stripes;
     const int64_t ring = std::min<int64_t>(kMaxRing, 2 * (int64_t)full3);
-    const bool chain = item_cap < ((int64_t)1 << 28) && sweep_ready(dev, c.stream, item_cap, ring);
-    const int grid3 = chain ? chain_grid(full3, n_pairs * stripes) : (int)std::min<int64_t>(full3, n_pairs);
+    const int cut3 = chain_grid(full3, n_pairs * stripes);
+    const bool chain = item_cap < ((int64_t)1 << 28) &&
+                       (!is_capturing(c.stream) || sweep_there(dev, c.stream, item_cap, ring, cut3));
+    const int grid3 = chain ? cut3 : (int)std::min<int64_t>(full3, n_pairs);
     StreamScratch *s = nullptr;
     rc = get_scratch(dev, c.stream, n_pairs, grid3, 0, false, true, s);
     if (rc) return rc;

@@ -1,0 +1,78 @@
+"""The C ABI on a recording HIP runtime (abi.cpp): its calls by name, with
+addresses that nothing reads."""
+import ctypes
+
+from paper_2310_05037_amd.lib import Opts
+
+from . import compile_host
+
+VP, I64 = ctypes.c_void_p, ctypes.c_int64
+P = VP(0x1000)
+
+
+class Abi:
+    def __init__(self):
+        self.so = so = compile_host("abi.cpp", "rawalign_abi.cpp")
+        so.mock_log.restype = so.mock_bad.restype = so.rawalign_last_error.restype = ctypes.c_char_p
+        so.mock_held.restype = ctypes.c_longlong
+        so.mock_limit.argtypes = [ctypes.c_longlong, ctypes.c_longlong]
+        self.stream = 1
+
+    def _rc(self, rc):
+        self.error = self.so.rawalign_last_error().decode() if rc else ""
+        return rc
+
+    def opts(self, **kw):
+        o = Opts()
+        self.so.rawalign_opts_default(ctypes.byref(o))
+        for k, v in kw.items():
+            setattr(o, k, v)
+        return o
+
+    def _pairs(self, n, q, r):
+        return [P, I64(q), P, P, P, I64(r), P, P]
+
+    def _o(self, opts):
+        return None if opts is None else ctypes.byref(opts)
+
+    def batch(self, n, q, r, opts=None):
+        return self._rc(self.so.rawalign_dtw_batch_ex(*self._pairs(n, q, r), I64(n), P, P, VP(self.stream), self._o(opts)))
+
+    def plain(self, n, q, r):
+        return self._rc(self.so.rawalign_dtw_batch(*self._pairs(n, q, r), I64(n), P, P, VP(self.stream)))
+
+    def extend(self, n, q, r, opts=None):
+        return self._rc(self.so.rawalign_dtw_extend(*self._pairs(n, q, r), P, I64(r), P, P, I64(n), P, P, VP(self.stream), self._o(opts)))
+
+    def span(self, n, q, r, opts=None):
+        return self._rc(self.so.rawalign_dtw_span(*self._pairs(n, q, r), I64(n), P, P, P, VP(self.stream), self._o(opts)))
+
+    def path(self, n, q, r, opts=None):
+        return self._rc(self.so.rawalign_dtw_path(*self._pairs(n, q, r), I64(n), P, P, I64(1 << 30), P, P, P, I64(1 << 30), P, P, P,
+                                                  VP(self.stream), self._o(opts)))
+
+    def band(self, n, q, r):
+        return self._rc(self.so.rawalign_dtw_band(*self._pairs(n, q, r), P, I64(n), P, P, VP(self.stream)))
+
+    def gaps(self, n, q, r, opts=None):
+        return self._rc(self.so.rawalign_dtw_global_batch(*self._pairs(n, q, r), I64(n), P, P, VP(self.stream), self._o(opts)))
+
+    def bnb(self, n, q, r, reads, max_query, opts=None):
+        d = ctypes.c_double
+        return self._rc(self.so.rawalign_map_bnb(*self._pairs(n, q, r), I64(n), P, P, P, I64(reads), d(0.4), d(20.0), max_query, 512, P,
+                                                 I64(r), P, P, P, P, P, P, VP(self.stream), self._o(opts)))
+
+    def capture(self, on):
+        self.so.mock_capture(int(on))
+
+    def limit(self, more=-1, largest=-1):
+        self.so.mock_limit(more, largest)
+
+    def held(self):
+        return self.so.mock_held()
+
+    def log(self):
+        return self.so.mock_log().decode().splitlines()
+
+    def bad(self):
+        return self.so.mock_bad().decode().splitlines()
