@@ -62,6 +62,7 @@ struct StreamScratch {
     int32_t *tiny_words = nullptr;   // one-pair-per-lane planning: hist | counts | base
     ra::TinyRec *tiny_list = nullptr;
     int64_t tiny_capacity = 0;
+    bool captured = false;      // a graph may hold these addresses
     hipStream_t sub[3] = {nullptr, nullptr, nullptr};
     hipEvent_t fork = nullptr;
     hipEvent_t gap_planned = nullptr;   // global calls: the gap plan on sub[0] is done
@@ -74,6 +75,7 @@ std::map<std::pair<int, hipStream_t>, StreamScratch> g_scratch;
 struct BnbStore {
     void *mem = nullptr;
     int64_t pairs = 0, reads = 0;
+    bool captured = false;
     ra::BnbScratch view;
 };
 std::map<std::pair<int, hipStream_t>, BnbStore> g_bnb;
@@ -83,6 +85,7 @@ std::map<std::pair<int, hipStream_t>, BnbStore> g_bnb;
 struct SpanStore {
     void *mem = nullptr;
     int64_t pairs = 0;
+    bool captured = false;
 };
 std::map<std::pair<int, hipStream_t>, SpanStore> g_span;
 
@@ -120,10 +123,20 @@ int alloc_fail(hipError_t e) {
     return fail(RAWALIGN_ENOMEM, std::string("scratch allocation: ") + hipGetErrorString(e));
 }
 
+// A buffer that a call outgrew.  Once a call was captured on the stream its graph
+// may be replayed with the old one, which then stays until process exit; from
+// there on buffers at least double (grown), so that what stays is no more than
+// is in use.
+void outgrown(bool captured, void *p) {
+    if (p && !captured) (void)hipFree(p);
+}
+int64_t grown(bool captured, int64_t need, int64_t have) { return captured ? std::max(need, 2 * have) : need; }
+
 int get_scratch(int dev, hipStream_t stream, int64_t n_pairs, int64_t edge_slots, int64_t row_slots, bool timing,
-                bool streams, StreamScratch *&out) {
+                bool streams, bool capture, StreamScratch *&out) {
     std::lock_guard<std::mutex> lk(g_mu);
     StreamScratch &s = g_scratch[{dev, stream}];
+    s.captured = s.captured || capture;
     hipError_t e;
     if (!s.words) {
         const size_t words = (size_t)ra::kNumRoutes * ra::kBuckets + 2 * ra::kNumRoutes;
@@ -136,7 +149,7 @@ int get_scratch(int dev, hipStream_t stream, int64_t n_pairs, int64_t edge_slots
     if (s.capacity < n_pairs) {
         int64_t cap = s.capacity ? s.capacity : 1024;
         while (cap < n_pairs) cap *= 2;
-        if (s.list) (void)hipFree(s.list);
+        outgrown(s.captured, s.list);
         s.list = nullptr;
         s.capacity = 0;
         e = hipMalloc((void **)&s.list, (size_t)cap * ra::kNumRoutes * sizeof(int32_t));
@@ -147,7 +160,8 @@ int get_scratch(int dev, hipStream_t stream, int64_t n_pairs, int64_t edge_slots
         s.capacity = cap;
     }
     if (s.edge_slots < edge_slots) {
-        if (s.edge) (void)hipFree(s.edge);
+        edge_slots = grown(s.captured, edge_slots, s.edge_slots);
+        outgrown(s.captured, s.edge);
         s.edge = nullptr;
         s.edge_slots = 0;
         e = hipMalloc((void **)&s.edge, (size_t)edge_slots * ra::kEdgeCap * sizeof(float));
@@ -158,7 +172,8 @@ int get_scratch(int dev, hipStream_t stream, int64_t n_pairs, int64_t edge_slots
         s.edge_slots = edge_slots;
     }
     if (s.row_slots < row_slots) {
-        if (s.rowbuf) (void)hipFree(s.rowbuf);
+        row_slots = grown(s.captured, row_slots, s.row_slots);
+        outgrown(s.captured, s.rowbuf);
         s.rowbuf = nullptr;
         s.row_slots = 0;
         e = hipMalloc((void **)&s.rowbuf, (size_t)row_slots * ra::kMaxRegion * sizeof(float));
@@ -209,7 +224,7 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
     }
     if (s.item_cap < item_cap) {
         const int64_t cap = std::max(item_cap, s.item_cap * 2);
-        if (s.items) (void)hipFree(s.items);
+        outgrown(s.captured, s.items);
         s.items = nullptr;
         s.item_cap = 0;
         e = hipMalloc((void **)&s.items, (size_t)cap * sizeof(uint64_t));
@@ -220,7 +235,8 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
         s.item_cap = cap;
     }
     if (s.ring_slots < ring_slots) {
-        if (s.ring) (void)hipFree(s.ring);
+        ring_slots = std::min(grown(s.captured, ring_slots, s.ring_slots), kMaxRing);
+        outgrown(s.captured, s.ring);
         s.ring = nullptr;
         s.ring_slots = 0;
         const size_t bytes = (size_t)ring_slots * ra::kSlotFloats * sizeof(float);
@@ -278,7 +294,7 @@ int get_tiny(StreamScratch &s, int64_t n_pairs) {
     if (s.tiny_capacity < n_pairs) {
         int64_t cap = s.tiny_capacity ? s.tiny_capacity : 1024;
         while (cap < n_pairs) cap *= 2;
-        if (s.tiny_list) (void)hipFree(s.tiny_list);
+        outgrown(s.captured, s.tiny_list);
         s.tiny_list = nullptr;
         s.tiny_capacity = 0;
         e = hipMalloc((void **)&s.tiny_list, (size_t)cap * sizeof(ra::TinyRec));
@@ -495,7 +511,7 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
             columns = std::max<int64_t>(own, std::min<int64_t>(grid_of(info.cus, o.long_waves_per_cu,
                                                                        ra::multi_blocks_per_cu(ext)), c.n_pairs));
         rc = get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing,
-                         capture ? concurrent : o.streams == 3, s);
+                         capture ? concurrent : o.streams == 3, capture, s);
         if (rc) return rc;
         if (cfg.chain) {
             rc = get_sweep(*s, c.stream, item_cap, ring, sw);
@@ -756,9 +772,10 @@ int rawalign_map_bnb(const float *q, int64_t q_size, const int64_t *q_off, const
     {
         std::lock_guard<std::mutex> lk(g_mu);
         BnbStore &b = g_bnb[{dev, st}];
+        b.captured = b.captured || is_capturing(st);
         const int64_t np = std::max<int64_t>(n_pairs, 1), nr = std::max<int64_t>(n_reads, 1);
         if (b.pairs < np || b.reads < nr) {
-            if (b.mem) (void)hipFree(b.mem);
+            outgrown(b.captured, b.mem);
             b.mem = nullptr;
             b.pairs = b.reads = 0;
             const int64_t P = std::max(np, 2 * b.pairs), R = std::max(nr, 2 * b.reads);
@@ -898,10 +915,11 @@ int rawalign_dtw_span(const float *q, int64_t q_size, const int64_t *q_off, cons
     {
         std::lock_guard<std::mutex> lk(g_mu);
         SpanStore &sp = g_span[{dev, st}];
+        sp.captured = sp.captured || is_capturing(st);
         if (sp.pairs < n_pairs) {
             int64_t cap = sp.pairs ? sp.pairs : 1024;
             while (cap < n_pairs) cap *= 2;
-            if (sp.mem) (void)hipFree(sp.mem);
+            outgrown(sp.captured, sp.mem);
             sp.mem = nullptr;
             sp.pairs = 0;
             hipError_t e = hipMalloc(&sp.mem, (size_t)cap * 12);
@@ -990,12 +1008,13 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
     ra::SweepScratch sw{};
     // Past the queue's range, and in a capture before the scratch is there, one
     // wave per pair.
-    if (item_cap >= ((int64_t)1 << 28) || (is_capturing(st) && !sweep_there(dev, st, item_cap, ring, 0))) {
+    const bool capture = is_capturing(st);
+    if (item_cap >= ((int64_t)1 << 28) || (capture && !sweep_there(dev, st, item_cap, ring, 0))) {
         const hipError_t e = ra::launch_path(pa, (int)n_pairs, sw, st);
         return e == hipSuccess ? RAWALIGN_OK : hip_fail(e, "path kernels");
     }
     StreamScratch *s = nullptr;
-    rc = get_scratch(dev, st, 0, 0, 0, false, false, s);
+    rc = get_scratch(dev, st, 0, 0, 0, false, false, capture, s);
     if (rc) return rc;
     rc = get_sweep(*s, st, item_cap, ring, sw);
     if (rc) return rc;
@@ -1027,11 +1046,12 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     const int64_t item_cap = n_pairs + (full3 + 64) * stripes;
     const int64_t ring = std::min<int64_t>(kMaxRing, 2 * (int64_t)full3);
     const int cut3 = chain_grid(full3, n_pairs * stripes);
+    const bool capture = is_capturing(c.stream);
     const bool chain = item_cap < ((int64_t)1 << 28) &&
-                       (!is_capturing(c.stream) || sweep_there(dev, c.stream, item_cap, ring, cut3));
+                       (!capture || sweep_there(dev, c.stream, item_cap, ring, cut3));
     const int grid3 = chain ? cut3 : (int)std::min<int64_t>(full3, n_pairs);
     StreamScratch *s = nullptr;
-    rc = get_scratch(dev, c.stream, n_pairs, grid3, 0, false, true, s);
+    rc = get_scratch(dev, c.stream, n_pairs, grid3, 0, false, true, capture, s);
     if (rc) return rc;
     ra::SweepScratch sw{};
     if (chain) {

@@ -77,3 +77,35 @@ def test_three_captured_sweeps_at_once(L):
         torch.cuda.synchronize()
         for b, db, _, _, ref in work:
             parity.check(b, *db.results(), ref=ref)
+
+
+def test_graph_after_calls_that_outgrow_its_scratch(L):
+    """Replays after uncaptured calls of the same stream on a longer reference
+    and of other entry points, which need larger scratch."""
+    import torch
+    rng = np.random.default_rng(12)
+    b = W.random_pairs(rng, 40, (300, 900), (900, 1800))
+    b.r, b.r_off = b.r[:1800], np.zeros_like(b.r_off)
+    db = L.DeviceBatch(b)
+    big = W.random_pairs(rng, 40, (300, 900), (2000, 20000))
+    dbig = L.DeviceBatch(big)
+    band = torch.full((40,), 300, dtype=torch.int32, device="cuda")
+    start = torch.empty(40, dtype=torch.int32, device="cuda")
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        db.run(opts=L.make_opts(), stream=st)
+    st.synchronize()
+    g = _capture(L, db, st)
+    ref = parity.oracle_batch(b)
+    a = (dbig.q, dbig.q_off, dbig.q_len, dbig.r, dbig.r_off, dbig.r_len)
+    later = [lambda: dbig.run(opts=L.make_opts(), stream=st),
+             lambda: L.rawalign_dtw_band(*a, band, dbig.score, dbig.end, stream=st),
+             lambda: L.rawalign_dtw_span(*a, dbig.score, dbig.end, start, stream=st)]
+    print("  gpu: graph after calls that outgrow its scratch", flush=True)
+    for call in later:
+        with torch.cuda.stream(st):
+            call()
+            db.score.fill_(-9.0)
+            g.replay()
+        torch.cuda.synchronize()
+        parity.check(b, *db.results(), ref=ref)
