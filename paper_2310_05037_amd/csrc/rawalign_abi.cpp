@@ -775,10 +775,11 @@ int rawalign_map_bnb(const float *q, int64_t q_size, const int64_t *q_off, const
         b.captured = b.captured || is_capturing(st);
         const int64_t np = std::max<int64_t>(n_pairs, 1), nr = std::max<int64_t>(n_reads, 1);
         if (b.pairs < np || b.reads < nr) {
+            const int64_t P = b.pairs < np ? std::max(np, 2 * b.pairs) : b.pairs;
+            const int64_t R = b.reads < nr ? std::max(nr, 2 * b.reads) : b.reads;
             outgrown(b.captured, b.mem);
             b.mem = nullptr;
             b.pairs = b.reads = 0;
-            const int64_t P = std::max(np, 2 * b.pairs), R = std::max(nr, 2 * b.reads);
             // 8-byte fields first, then 4-byte, then 1-byte: every field stays aligned.
             const size_t bytes = (size_t)R * 8 + (size_t)P * (8 + 5 * 4 + 2);
             hipError_t e = hipMalloc(&b.mem, bytes);
