@@ -22,8 +22,10 @@ def _moves(A, sizes):
 
 
 def test_growing_batches(A):
+    """From 100 to 3,000 pairs, five doublings, and as many of the reads, which
+    may fall on other calls; and the first."""
     A.stream += 1
-    assert _moves(A, [(n, n // 4 + 1) for n in range(100, 3000, 20)]) <= 7
+    assert _moves(A, [(n, n // 4 + 1) for n in range(100, 3000, 20)]) <= 11
 
 
 def test_more_pairs_and_more_reads_in_turn(A):
