@@ -126,8 +126,9 @@ int rawalign_opts_default(rawalign_opts *opts);
  * the stream; calls on different streams use different scratch.  Growing the
  * scratch calls hipMalloc, so a call that may be captured into a HIP graph
  * must follow an uncaptured call of at least the same n_pairs on that stream;
- * captured before the sweep's own scratch is there, a call takes the kernels
- * of plain mode's routes in persistent queues instead.  Scratch that a
+ * captured before the sweep's own scratch is there, and where there is no room
+ * for it, a call takes the kernels of plain mode's routes in persistent queues
+ * instead.  Scratch that a
  * captured call used is kept when a later call on the stream outgrows it, so
  * the graph stays valid (at most as much again as is in use).  A sweep whose waves
  * wait for each other longer than 5 s (a GPU that does not run them) ends with

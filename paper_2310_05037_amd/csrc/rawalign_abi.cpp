@@ -120,6 +120,7 @@ int device_info(int &dev, DeviceInfo &info) {
 }
 
 int alloc_fail(hipError_t e) {
+    (void)hipGetLastError();   // a call that goes on without this buffer does not report it
     return fail(RAWALIGN_ENOMEM, std::string("scratch allocation: ") + hipGetErrorString(e));
 }
 
@@ -470,29 +471,24 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         own = levels > ra::kSweepStripe ? cfg.sweep_grid : 0;
         cfg.chain = !capture || sweep_there(dev, c.stream, item_cap, ring, own);
     }
-    if (!cfg.chain) {
-        cfg.lo_grid = grid_of(info.cus, o.lo_waves_per_cu, ra::single_lo_blocks_per_cu(ext));
-        cfg.multi_grid = grid_of(info.cus, o.long_waves_per_cu, ra::multi_blocks_per_cu(ext));
-    }
-    cfg.hi_grid = grid_of(info.cus, o.hi_waves_per_cu, ra::single_hi_blocks_per_cu(ext));
+    // A persistent grid never needs more workgroups than the batch has pairs
+    // (a small batch would otherwise launch thousands of waves that only start
+    // and exit).
+    const int cap = (int)std::min<int64_t>(c.n_pairs, 1 << 30);
+    // The routes of whole pairs, where the sweep does not take them.
+    auto whole_pairs = [&]() {
+        cfg.chain = false;
+        cfg.lo_grid = std::min(cap, grid_of(info.cus, o.lo_waves_per_cu, ra::single_lo_blocks_per_cu(ext)));
+        cfg.multi_grid = std::min(cap, grid_of(info.cus, o.long_waves_per_cu, ra::multi_blocks_per_cu(ext)));
+    };
+    if (!cfg.chain) whole_pairs();
+    cfg.hi_grid = std::min(cap, grid_of(info.cus, o.hi_waves_per_cu, ra::single_hi_blocks_per_cu(ext)));
     // Anti-diagonal kernel: opts.long_waves_per_cu counts its workgroups per
     // CU; by default its occupancy limit (5: LDS and registers), each with a
     // 256 KiB row buffer.
     const int ad_occ = ra::antidiag_blocks_per_cu();
-    cfg.antidiag_grid = info.cus * (o.long_waves_per_cu ? std::min(o.long_waves_per_cu, ad_occ) : ad_occ);
-    // A persistent grid never needs more workgroups than the batch has pairs
-    // or items (a small batch would otherwise launch thousands of waves that
-    // only start and exit).
-    {
-        const int cap = (int)std::min<int64_t>(c.n_pairs, 1 << 30);
-        cfg.lo_grid = std::min(cfg.lo_grid, cap);
-        cfg.hi_grid = std::min(cfg.hi_grid, cap);
-        cfg.multi_grid = std::min(cfg.multi_grid, cap);
-        cfg.antidiag_grid = std::min(cfg.antidiag_grid, cap);
-    }
-
+    cfg.antidiag_grid = std::min(cap, info.cus * (o.long_waves_per_cu ? std::min(o.long_waves_per_cu, ad_occ) : ad_occ));
     const bool timing = (o.flags & RAWALIGN_FLAG_TIMING) != 0;
-    const bool concurrent = o.streams == 3 && !cfg.chain;
     StreamScratch *s = nullptr;
     ra::PlanScratch fixed;
     ra::SweepScratch sw{};
@@ -506,19 +502,22 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
         // A call that may allocate also gets what a captured call of no more
         // pairs needs if it cannot have the sweep's: the former's, and the
         // internal streams.
-        int64_t columns = cfg.chain ? own : cfg.multi_grid;
-        if (cfg.chain && !capture)
-            columns = std::max<int64_t>(own, std::min<int64_t>(grid_of(info.cus, o.long_waves_per_cu,
-                                                                       ra::multi_blocks_per_cu(ext)), c.n_pairs));
-        rc = get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing,
-                         capture ? concurrent : o.streams == 3, capture, s);
-        if (rc) return rc;
+        auto scratch = [&](int64_t columns) {
+            return get_scratch(dev, c.stream, c.n_pairs, columns, antidiag ? cfg.antidiag_grid : 0, timing,
+                               o.streams == 3 && !(capture && cfg.chain), capture, s);
+        };
         if (cfg.chain) {
-            rc = get_sweep(*s, c.stream, item_cap, ring, sw);
-            if (rc) return rc;
-            sw.own = s->edge;
+            rc = scratch(capture ? own
+                                 : std::max<int64_t>(own, std::min(cap, grid_of(info.cus, o.long_waves_per_cu,
+                                                                                ra::multi_blocks_per_cu(ext)))));
+            if (!rc) rc = get_sweep(*s, c.stream, item_cap, ring, sw);
+            if (!rc) sw.own = s->edge;
+            else if (rc != RAWALIGN_ENOMEM) return rc;
+            else whole_pairs();   // no room for the sweep's: the routes that need none of it
         }
+        if (!cfg.chain && (rc = scratch(cfg.multi_grid)) != RAWALIGN_OK) return rc;
     }
+    const bool concurrent = o.streams == 3 && !cfg.chain;
 
     ra::PairArrays a;
     a.q = c.q;
@@ -1007,18 +1006,21 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
     const int64_t item_cap = n_pairs * (levels / ra::kSweepStripe + 2) + 3 * (int64_t)grid;
     const int64_t ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)grid));
     ra::SweepScratch sw{};
-    // Past the queue's range, and in a capture before the scratch is there, one
-    // wave per pair.
+    // Past the queue's range, in a capture before the scratch is there and where
+    // there is no room for it, one wave per pair.
     const bool capture = is_capturing(st);
-    if (item_cap >= ((int64_t)1 << 28) || (capture && !sweep_there(dev, st, item_cap, ring, 0))) {
-        const hipError_t e = ra::launch_path(pa, (int)n_pairs, sw, st);
+    StreamScratch *s = nullptr;
+    bool chain = item_cap < ((int64_t)1 << 28) && (!capture || sweep_there(dev, st, item_cap, ring, 0));
+    if (chain) {
+        rc = get_scratch(dev, st, 0, 0, 0, false, false, capture, s);
+        if (!rc) rc = get_sweep(*s, st, item_cap, ring, sw);
+        if (rc && rc != RAWALIGN_ENOMEM) return rc;
+        chain = !rc;
+    }
+    if (!chain) {
+        const hipError_t e = ra::launch_path(pa, (int)n_pairs, ra::SweepScratch{}, st);
         return e == hipSuccess ? RAWALIGN_OK : hip_fail(e, "path kernels");
     }
-    StreamScratch *s = nullptr;
-    rc = get_scratch(dev, st, 0, 0, 0, false, false, capture, s);
-    if (rc) return rc;
-    rc = get_sweep(*s, st, item_cap, ring, sw);
-    if (rc) return rc;
     hipError_t e = ra::launch_path_plan(pa, grid, plan_view(*s), sw, st);
     if (e != hipSuccess) return hip_fail(e, "path planning");
     e = ra::launch_path(pa, grid, sw, st);
@@ -1048,18 +1050,21 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     const int64_t ring = std::min<int64_t>(kMaxRing, 2 * (int64_t)full3);
     const int cut3 = chain_grid(full3, n_pairs * stripes);
     const bool capture = is_capturing(c.stream);
-    const bool chain = item_cap < ((int64_t)1 << 28) &&
-                       (!capture || sweep_there(dev, c.stream, item_cap, ring, cut3));
-    const int grid3 = chain ? cut3 : (int)std::min<int64_t>(full3, n_pairs);
+    bool chain = item_cap < ((int64_t)1 << 28) && (!capture || sweep_there(dev, c.stream, item_cap, ring, cut3));
     StreamScratch *s = nullptr;
-    rc = get_scratch(dev, c.stream, n_pairs, grid3, 0, false, true, capture, s);
-    if (rc) return rc;
     ra::SweepScratch sw{};
+    auto scratch = [&](int64_t columns) {
+        return get_scratch(dev, c.stream, n_pairs, columns, 0, false, true, capture, s);
+    };
     if (chain) {
-        rc = get_sweep(*s, c.stream, item_cap, ring, sw);
-        if (rc) return rc;
-        sw.own = s->edge;
+        rc = scratch(cut3);
+        if (!rc) rc = get_sweep(*s, c.stream, item_cap, ring, sw);
+        if (rc && rc != RAWALIGN_ENOMEM) return rc;
+        chain = !rc;   // no room: every pair on one wave
+        if (chain) sw.own = s->edge;
     }
+    const int grid3 = chain ? cut3 : (int)std::min<int64_t>(full3, n_pairs);
+    if (!chain && (rc = scratch(grid3)) != RAWALIGN_OK) return rc;
     ra::PairArrays a;
     a.q = q;
     a.q_size = q_size;
