@@ -120,9 +120,13 @@ int rawalign_opts_default(rawalign_opts *opts);
  *                 region where the best path ends (smallest on ties)
  *
  * Internal scratch (planning lists, queue counters, and for persistent calls
- * the stripe sweep's work items and edge columns, up to 0.9 GB) is allocated
- * by the library per (device, stream) on first use, grown when a larger batch
- * arrives and kept until process exit.  Calls on one stream are ordered by
+ * the stripe sweep's edge columns and work items) is allocated by the library
+ * per (device, stream) on first use, grown when a larger batch arrives and kept
+ * until process exit.  Edge columns: twice 64 KB for each work item that the
+ * pairs can have with q_size events and r_size levels, 43 MB for ten candidates
+ * of a read of 1,500 events in a large reference, and 0.9 GB at most.  Work
+ * items: 8 bytes each, up to 34 a pair with a long reference (0.27 GB for a
+ * million pairs).  Calls on one stream are ordered by
  * the stream; calls on different streams use different scratch.  Growing the
  * scratch calls hipMalloc, so a call that may be captured into a HIP graph
  * must follow an uncaptured call of at least the same n_pairs on that stream;

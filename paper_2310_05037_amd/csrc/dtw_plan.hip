@@ -450,21 +450,21 @@ hipError_t launch_plan(const PairArrays &a, int64_t n_pairs, const LaunchCfg &cf
     pa.chain = cfg.chain;
     pa.few = cfg.sweep_few;
     pa.chain_route = kRouteSingleLo;
-    pa.lim_scale = kItemShare / (64.0f * (float)(cfg.sweep_grid > 0 ? cfg.sweep_grid : 1));
+    pa.lim_scale = kItemShare / (64.0f * (float)(cfg.sweep_share > 0 ? cfg.sweep_share : 1));
     pa.s = s;
     if (cfg.chain) pa.sw = *sw;
     pa.band = nullptr;
     return run_plan(pa, stream);
 }
 
-hipError_t launch_path_plan(const PathArgs &path, int grid, const PlanScratch &s, const SweepScratch &sw,
+hipError_t launch_path_plan(const PathArgs &path, int share, const PlanScratch &s, const SweepScratch &sw,
                             hipStream_t stream) {
     PlanArgs pa{};
     pa.n_pairs = path.n_pairs;
     pa.buckets = kBuckets;
     pa.chain = 1;
     pa.chain_route = kRouteSingleLo;
-    pa.lim_scale = kItemShare / (64.0f * (float)grid);
+    pa.lim_scale = kItemShare / (64.0f * (float)share);
     pa.s = s;
     pa.sw = sw;
     pa.paths = 1;

@@ -36,6 +36,12 @@ RA_HOST_DEV inline void sweep_shape(int n, int m, float lim, int &items, int &k,
     if (items > 1) items = (m + 64 * c - 1) / (64 * c);   // every item starts inside the region
 }
 
+// Work items a pair of at most n events and m levels can have, whatever lim.
+RA_HOST_DEV inline int64_t most_items(int64_t n, int64_t m) {
+    const float rows = (float)(n < 1 ? 1 : n < kEdgeCap ? n : kEdgeCap), cols = (float)(m < 1 ? 1 : m < kMaxRegion ? m : kMaxRegion);
+    const float most = cols / (64.0f * fmaxf((float)kSweepMinC, sqrtf(26.0f * cols / rows)));
+    return (int64_t)fmaxf(most, cols / (float)kSweepStripe) + 2;   // rounded up, and what rounding may add
+}
 static_assert(kEdgeCap + 3 <= kSlotFloats, "an edge column fits its slot");
 
 }  // namespace ra

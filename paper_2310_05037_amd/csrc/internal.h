@@ -238,7 +238,8 @@ struct BnbArgs {
 struct LaunchCfg {
     bool persistent;    // atomic queue + LPT order (else static assignment, arrival order)
     bool chain;         // the stripe sweep takes every pair but over-long queries
-    int sweep_grid;     // grid sizes (workgroups of one wave); waves of the sweep resident at once
+    int sweep_grid;     // grid sizes (workgroups of one wave)
+    int sweep_share;    // waves of the sweep that the planner shares the batch out to
     int sweep_few;      // what of it large batches of long pairs take
     int lo_grid;
     int hi_grid;

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "dtw_path.h"
+#include "dtw_shape.h"
 #include "internal.h"
 #include "rawalign.h"
 
@@ -209,7 +210,13 @@ int get_scratch(int dev, hipStream_t stream, int64_t n_pairs, int64_t edge_slots
 // Scratch of the chained sweep: work items, the ring of edge columns (filled
 // with its empty mark on `stream`, ahead of the kernels) and its counters.
 constexpr int64_t kMaxRing = 8192;
-int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ring_slots, ra::SweepScratch &out) {
+// What a chained call needs of it.
+struct SweepNeed {
+    int64_t items = 0;
+    int64_t slots = 0;      // ring slots
+    int64_t columns = 0;    // edge columns of kOwnFloats
+};
+int get_sweep(StreamScratch &s, hipStream_t stream, const SweepNeed &need, ra::SweepScratch &out) {
     std::lock_guard<std::mutex> lk(g_mu);
     hipError_t e;
     const size_t line = ra::kQueueStride * sizeof(int32_t);
@@ -223,8 +230,8 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
         e = hipMemsetAsync(s.sweep_words, 0, head + kMaxRing * sizeof(int32_t), stream);
         if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
     }
-    if (s.item_cap < item_cap) {
-        const int64_t cap = std::max(item_cap, s.item_cap * 2);
+    if (s.item_cap < need.items) {
+        const int64_t cap = std::max(need.items, s.item_cap * 2);
         outgrown(s.captured, s.items);
         s.items = nullptr;
         s.item_cap = 0;
@@ -235,12 +242,12 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
         }
         s.item_cap = cap;
     }
-    if (s.ring_slots < ring_slots) {
-        ring_slots = std::min(grown(s.captured, ring_slots, s.ring_slots), kMaxRing);
+    if (s.ring_slots < need.slots) {
+        const int64_t slots = std::min(grown(s.captured, need.slots, s.ring_slots), kMaxRing);
         outgrown(s.captured, s.ring);
         s.ring = nullptr;
         s.ring_slots = 0;
-        const size_t bytes = (size_t)ring_slots * ra::kSlotFloats * sizeof(float);
+        const size_t bytes = (size_t)slots * ra::kSlotFloats * sizeof(float);
         e = hipMalloc((void **)&s.ring, bytes);
         if (e != hipSuccess) {
             s.ring = nullptr;
@@ -248,7 +255,7 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
         }
         e = hipMemsetAsync(s.ring, 0xff, bytes, stream);
         if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
-        s.ring_slots = ring_slots;
+        s.ring_slots = slots;
     }
     out.partial = (double *)s.sweep_words;
     out.n_items = (int32_t *)(out.partial + ra::kPlanGrid);
@@ -259,6 +266,7 @@ int get_sweep(StreamScratch &s, hipStream_t stream, int64_t item_cap, int64_t ri
     out.item_cap = s.item_cap;
     out.ring = s.ring;
     out.ring_slots = (int)s.ring_slots;
+    out.own = s.edge;
     return RAWALIGN_OK;
 }
 
@@ -274,10 +282,17 @@ bool is_capturing(hipStream_t stream) {
 // All that a chained call needs is there: its work items, ring slots and edge
 // columns.  A captured call, which may not allocate, takes the routes that need
 // none of them otherwise.
-bool sweep_there(int dev, hipStream_t stream, int64_t item_cap, int64_t ring_slots, int64_t columns) {
+bool sweep_there(int dev, hipStream_t stream, const SweepNeed &need) {
     std::lock_guard<std::mutex> lk(g_mu);
     const StreamScratch &s = g_scratch[{dev, stream}];
-    return s.item_cap >= item_cap && s.ring_slots >= ring_slots && s.edge_slots >= columns;
+    return s.item_cap >= need.items && s.ring_slots >= need.slots && s.edge_slots >= need.columns;
+}
+
+// Ring slots of a launch of `grid` workgroups for at most `items` items: two for
+// each wave, so that a column can wait for its reader while the next is written,
+// and no more than there are items.
+int64_t ring_of(int grid, int64_t items) {
+    return std::min(kMaxRing, std::max<int64_t>(8, std::min<int64_t>(2 * (int64_t)grid, items)));
 }
 
 // Planning scratch of the one-pair-per-lane kernel (global calls only).
@@ -454,22 +469,25 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
     const int64_t full_stripes = c.n_pairs * ((levels + ra::kSweepStripe - 1) / ra::kSweepStripe + 1);
     cfg.chain = cfg.persistent && !tiny && !noalloc && !antidiag && full_stripes < ((int64_t)1 << 28);
     cfg.single_max = o.single_max ? o.single_max : ra::kSingleMaxRegion;
-    cfg.lo_grid = cfg.multi_grid = cfg.sweep_grid = cfg.sweep_few = 0;
+    cfg.lo_grid = cfg.multi_grid = cfg.sweep_grid = cfg.sweep_share = cfg.sweep_few = 0;
     const bool capture = !noalloc && is_capturing(c.stream);
-    int64_t ring = 0, item_cap = 0, own = 0;
+    SweepNeed need;
     if (cfg.chain) {
         // One kernel takes all three routes: the widest of their grids.
         const int occ = ra::sweep_blocks_per_cu(ext);
         const int w[3] = {o.lo_waves_per_cu, o.hi_waves_per_cu, o.long_waves_per_cu};
         const bool full = !w[0] || !w[1] || !w[2];
         const int64_t narrow = 64 * ra::kSweepMinC;
-        cfg.sweep_grid = info.cus * (full ? occ : std::min(occ, std::max({w[0], w[1], w[2]})));
-        cfg.sweep_grid = chain_grid(cfg.sweep_grid, c.n_pairs * ((levels + narrow - 1) / narrow + 1));
+        const int resident = info.cus * (full ? occ : std::min(occ, std::max({w[0], w[1], w[2]})));
+        const int64_t longest = std::min(c.q_size, c.max_query);
+        const int64_t items = c.n_pairs * ra::most_items(longest, levels);
+        cfg.sweep_share = chain_grid(resident, c.n_pairs * ((levels + narrow - 1) / narrow + 1));
+        cfg.sweep_grid = chain_grid(resident, items);
         cfg.sweep_few = full ? std::min(cfg.sweep_grid, 16 * info.cus) : cfg.sweep_grid;
-        ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)cfg.sweep_grid));
-        item_cap = full_stripes + 3 * (int64_t)cfg.sweep_grid;
-        own = levels > ra::kSweepStripe ? cfg.sweep_grid : 0;
-        cfg.chain = !capture || sweep_there(dev, c.stream, item_cap, ring, own);
+        need.items = std::min(items, full_stripes + 3 * (int64_t)cfg.sweep_share);
+        need.slots = ring_of(cfg.sweep_grid, items);
+        need.columns = levels > ra::kSweepStripe ? cfg.sweep_grid : 0;
+        cfg.chain = !capture || sweep_there(dev, c.stream, need);
     }
     // A persistent grid never needs more workgroups than the batch has pairs
     // (a small batch would otherwise launch thousands of waves that only start
@@ -507,13 +525,11 @@ int run(const Call &c, const rawalign_opts &o, bool noalloc = false) {
                                o.streams == 3 && !(capture && cfg.chain), capture, s);
         };
         if (cfg.chain) {
-            rc = scratch(capture ? own
-                                 : std::max<int64_t>(own, std::min(cap, grid_of(info.cus, o.long_waves_per_cu,
-                                                                                ra::multi_blocks_per_cu(ext)))));
-            if (!rc) rc = get_sweep(*s, c.stream, item_cap, ring, sw);
-            if (!rc) sw.own = s->edge;
-            else if (rc != RAWALIGN_ENOMEM) return rc;
-            else whole_pairs();   // no room for the sweep's: the routes that need none of it
+            const int multi = std::min(cap, grid_of(info.cus, o.long_waves_per_cu, ra::multi_blocks_per_cu(ext)));
+            rc = scratch(capture ? need.columns : std::max<int64_t>(need.columns, multi));
+            if (!rc) rc = get_sweep(*s, c.stream, need, sw);
+            if (rc && rc != RAWALIGN_ENOMEM) return rc;
+            if (rc) whole_pairs();   // no room for the sweep's: the routes that need none of it
         }
         if (!cfg.chain && (rc = scratch(cfg.multi_grid)) != RAWALIGN_OK) return rc;
     }
@@ -1002,18 +1018,20 @@ int rawalign_dtw_path(const float *q, int64_t q_size, const int64_t *q_off, cons
     // Items: one per pair, one per 2,048 columns and what the planner's share
     // adds (path_shape: c is at most twice the least).
     const int64_t levels = std::min<int64_t>(r_size, ra::kMaxRegion);
-    const int grid = chain_grid(info.cus * ra::path_blocks_per_cu(), n_pairs * (levels / 256 + 1));
-    const int64_t item_cap = n_pairs * (levels / ra::kSweepStripe + 2) + 3 * (int64_t)grid;
-    const int64_t ring = std::min<int64_t>(kMaxRing, std::max<int64_t>(256, 2 * (int64_t)grid));
+    const int64_t items = n_pairs * (levels / 256 + 1);
+    const int grid = chain_grid(info.cus * ra::path_blocks_per_cu(), items);
+    SweepNeed need;
+    need.items = std::min(items, n_pairs * (levels / ra::kSweepStripe + 2) + 3 * (int64_t)grid);
+    need.slots = ring_of(grid, items);
     ra::SweepScratch sw{};
     // Past the queue's range, in a capture before the scratch is there and where
     // there is no room for it, one wave per pair.
     const bool capture = is_capturing(st);
     StreamScratch *s = nullptr;
-    bool chain = item_cap < ((int64_t)1 << 28) && (!capture || sweep_there(dev, st, item_cap, ring, 0));
+    bool chain = need.items < ((int64_t)1 << 28) && (!capture || sweep_there(dev, st, need));
     if (chain) {
         rc = get_scratch(dev, st, 0, 0, 0, false, false, capture, s);
-        if (!rc) rc = get_sweep(*s, st, item_cap, ring, sw);
+        if (!rc) rc = get_sweep(*s, st, need, sw);
         if (rc && rc != RAWALIGN_ENOMEM) return rc;
         chain = !rc;
     }
@@ -1046,22 +1064,23 @@ int rawalign_dtw_band(const float *q, int64_t q_size, const int64_t *q_off, cons
     // gives each resident wave an edge column.
     const int64_t stripes = std::min<int64_t>(r_size, ra::kMaxRegion) / 256 + 1;
     const int full3 = info.cus * ra::band_blocks_per_cu(3);
-    const int64_t item_cap = n_pairs + (full3 + 64) * stripes;
-    const int64_t ring = std::min<int64_t>(kMaxRing, 2 * (int64_t)full3);
     const int cut3 = chain_grid(full3, n_pairs * stripes);
+    SweepNeed need;
+    need.items = std::min(n_pairs * stripes, n_pairs + (full3 + 64) * stripes);
+    need.slots = ring_of(cut3, n_pairs * stripes);
+    need.columns = cut3;
     const bool capture = is_capturing(c.stream);
-    bool chain = item_cap < ((int64_t)1 << 28) && (!capture || sweep_there(dev, c.stream, item_cap, ring, cut3));
+    bool chain = need.items < ((int64_t)1 << 28) && (!capture || sweep_there(dev, c.stream, need));
     StreamScratch *s = nullptr;
     ra::SweepScratch sw{};
     auto scratch = [&](int64_t columns) {
         return get_scratch(dev, c.stream, n_pairs, columns, 0, false, true, capture, s);
     };
     if (chain) {
-        rc = scratch(cut3);
-        if (!rc) rc = get_sweep(*s, c.stream, item_cap, ring, sw);
+        rc = scratch(need.columns);
+        if (!rc) rc = get_sweep(*s, c.stream, need, sw);
         if (rc && rc != RAWALIGN_ENOMEM) return rc;
         chain = !rc;   // no room: every pair on one wave
-        if (chain) sw.own = s->edge;
     }
     const int grid3 = chain ? cut3 : (int)std::min<int64_t>(full3, n_pairs);
     if (!chain && (rc = scratch(grid3)) != RAWALIGN_OK) return rc;

@@ -448,7 +448,9 @@ class GpuBackend:
     flight at once, each with its own tables, stream and graph (launch/poll):
     a chunk that becomes available while a tick runs does not wait for it.
     Ticks in flight never share a read (a read's next chunk is scheduled only
-    after its results are back), so their rows are disjoint."""
+    after its results are back), so their rows are disjoint.  The library's
+    scratch comes on top of the arena and the tables: per slot, as for a batch
+    of max_jobs pairs on its stream (up to 0.9 GB of edge columns)."""
 
     def __init__(self, r_levels: np.ndarray, arena_floats: int, chunk: int = 400, max_jobs: int = 1 << 15,
                  max_reads: int = 4096, use_graph: bool = True, opts=None, slots: int = 2):

@@ -3,6 +3,7 @@
 // runs without a GPU.  Device memory is addresses only.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <map>
 #include <set>
@@ -49,6 +50,7 @@ void use_sweep(const ra::SweepScratch &sw, int grid, bool own) {
     if (grid < ra::kCover) wrong("a chained launch of " + str(grid) + " workgroups");
     use("items", sw.items, sizeof(uint64_t) * sw.item_cap);
     use("ring", sw.ring, sizeof(float) * (size_t)sw.ring_slots * ra::kSlotFloats);
+    if (sw.ring_slots < 2) wrong("ring slots");
     if (own) use("own columns", sw.own, sizeof(float) * (size_t)grid * ra::kOwnFloats);
     use("done", sw.done, sizeof(int32_t) * sw.ring_slots);
     use("queue", sw.queue, sizeof(int32_t) * ra::kQueues * ra::kQueueStride);
