@@ -182,13 +182,13 @@ RA_DEV uint64_t path_codes(const char *row, int jb, int words) {
     return sh ? lo >> sh | hi << (64 - sh) : lo;
 }
 
-// plan: SweepScratch::n_items of the direction pass, null if it had no queue.
-__global__ __launch_bounds__(64) void k_path_trace(PathArgs pa, const int32_t *plan) {
+// plan, failed: SweepScratch's of the direction pass, null if it had no queue.
+__global__ __launch_bounds__(64) void k_path_trace(PathArgs pa, const int32_t *plan, const int32_t *failed) {
     const int lane = __lane_id();
     for (int64_t p = blockIdx.x; p < pa.n_pairs; p += gridDim.x) {
         int n = 0, s = 0, L = 0;
         int st = path_interval(pa, p, n, s, L);
-        if (st == 0 && plan && path_lost(n, L, reinterpret_cast<const float *>(plan)[3], plan[1] != 0)) st = kGaveUp;
+        if (st == 0 && plan && path_lost(n, L, reinterpret_cast<const float *>(plan)[3], *failed != 0)) st = kGaveUp;
         st = __builtin_amdgcn_readfirstlane(st);
         s = __builtin_amdgcn_readfirstlane(s);
         const int64_t off = pa.path_off[p];
@@ -249,7 +249,8 @@ int path_blocks_per_cu() {
 hipError_t launch_path(const PathArgs &pa, int grid, const SweepScratch &sw, hipStream_t stream) {
     hipLaunchKernelGGL(k_path_dirs, dim3((unsigned)grid), dim3(64), 0, stream, pa, sw);
     const unsigned g = (unsigned)(pa.n_pairs < (1 << 20) ? pa.n_pairs : (1 << 20));
-    hipLaunchKernelGGL(k_path_trace, dim3(g), dim3(64), 0, stream, pa, sw.items ? sw.n_items : nullptr);
+    hipLaunchKernelGGL(k_path_trace, dim3(g), dim3(64), 0, stream, pa, sw.items ? sw.n_items : nullptr,
+                       sw.failed);
     return hipGetLastError();
 }
 

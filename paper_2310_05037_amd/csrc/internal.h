@@ -123,13 +123,13 @@ RA_HOST_DEV constexpr int span_start(int end, int rev_end) {
 struct SweepScratch {
     uint64_t *items;      // [item_cap] work items, pairs longest first, stripes in order
     int64_t item_cap;
-    int32_t *n_items;     // [4] items; failed; workgroups that take items (live_workgroups); the share (float bits)
+    int32_t *n_items;     // [4] items; unused; workgroups that take items (live_workgroups); the share (float bits)
     int32_t *queue;       // [kQueues * kQueueStride] work-queue heads
     float *ring;          // [ring_slots * kSlotFloats] edge columns between items
     float *own;           // [grid * kOwnFloats] edge columns within an item
     int ring_slots;
     int32_t *done;        // [ring_slots] item after the one whose column was consumed last
-    int32_t *failed;      // a wait timed out: the next planner refills the ring
+    int32_t *failed;      // behind the ring: a wait timed out, its next planner refills it
     double *partial;      // [kPlanGrid] cells of each planning workgroup's pairs
 };
 

@@ -248,24 +248,25 @@ int get_sweep(StreamScratch &s, hipStream_t stream, const SweepNeed &need, ra::S
         s.ring = nullptr;
         s.ring_slots = 0;
         const size_t bytes = (size_t)slots * ra::kSlotFloats * sizeof(float);
-        e = hipMalloc((void **)&s.ring, bytes);
+        e = hipMalloc((void **)&s.ring, bytes + sizeof(int32_t));   // and its failure flag
         if (e != hipSuccess) {
             s.ring = nullptr;
             return alloc_fail(e);
         }
         e = hipMemsetAsync(s.ring, 0xff, bytes, stream);
+        if (e == hipSuccess) e = hipMemsetAsync((char *)s.ring + bytes, 0, sizeof(int32_t), stream);
         if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
         s.ring_slots = slots;
     }
     out.partial = (double *)s.sweep_words;
     out.n_items = (int32_t *)(out.partial + ra::kPlanGrid);
-    out.failed = out.n_items + 1;
     out.queue = out.n_items + ra::kQueueStride;
     out.done = out.queue + ra::kQueues * ra::kQueueStride;
     out.items = s.items;
     out.item_cap = s.item_cap;
     out.ring = s.ring;
     out.ring_slots = (int)s.ring_slots;
+    out.failed = (int32_t *)(s.ring + (size_t)s.ring_slots * ra::kSlotFloats);
     out.own = s.edge;
     return RAWALIGN_OK;
 }

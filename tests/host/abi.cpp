@@ -51,6 +51,10 @@ void use_sweep(const ra::SweepScratch &sw, int grid, bool own) {
     use("items", sw.items, sizeof(uint64_t) * sw.item_cap);
     use("ring", sw.ring, sizeof(float) * (size_t)sw.ring_slots * ra::kSlotFloats);
     if (sw.ring_slots < 2) wrong("ring slots");
+    use("failure flag", sw.failed, sizeof(int32_t));
+    auto ring = --g.live.upper_bound((uintptr_t)sw.ring), flag = --g.live.upper_bound((uintptr_t)sw.failed);
+    if (ring != flag || (uintptr_t)sw.failed < (uintptr_t)(sw.ring + (size_t)sw.ring_slots * ra::kSlotFloats))
+        wrong("the failure flag is not beside its ring");
     if (own) use("own columns", sw.own, sizeof(float) * (size_t)grid * ra::kOwnFloats);
     use("done", sw.done, sizeof(int32_t) * sw.ring_slots);
     use("queue", sw.queue, sizeof(int32_t) * ra::kQueues * ra::kQueueStride);

@@ -65,3 +65,13 @@ def test_what_is_kept_is_bounded(A):
     A.stream += 1
     _capture(A, A.batch, 1, 1000, 1000)
     assert grow() <= 4 * free and A.bad() == []
+
+
+def test_the_failure_flag_belongs_to_its_ring(A):
+    """A wait given up in a replay leaves the graph's ring to be refilled by the
+    graph's next planner, whatever eager calls on a newer ring do in between: the
+    launches check that the flag lies behind the ring they use."""
+    _capture(A, A.batch, 3, 1000, 1000)
+    for n in (40, 400, 4000):
+        assert A.batch(n, 10 ** 6, 10 ** 6) == 0 and A.path(n, 10 ** 6, 10 ** 6) == 0 and A.band(n, 10 ** 6, 10 ** 6) == 0
+    assert A.bad() == []
