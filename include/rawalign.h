@@ -447,8 +447,9 @@ int rawalign_chain_decide(const float *gap_cost, int64_t n_gaps, const int64_t *
  *   1. the kernel shape: the stripe sweep, or the anti-diagonal kernel
  *      (RAWALIGN_LONG_ANTIDIAG) for regions above a single-stripe cut-off of
  *      4096 or 2048 levels;
- *   2. at that shape: the persistent grids at or below occupancy, and one or
- *      three streams beside the anti-diagonal kernel.
+ *   2. for the anti-diagonal kernel, its workgroups per CU at or below
+ *      occupancy, and one or three streams beside it (the stripe sweep's waves
+ *      are the planner's choice for each batch).
  * Every candidate returns the same bits, so the choice affects time only.
  * The anti-diagonal kernel serves plain batches only: calls of the other
  * entry points that inherit a tuned setting naming it (opts NULL) take the
@@ -466,7 +467,9 @@ int rawalign_autotune(const float *q, int64_t q_size, const int64_t *q_off, cons
                       const char *cache_path, rawalign_opts *best);
 
 /* Load a tuning cache written by rawalign_autotune; entries for other
- * devices or library versions are ignored (returns RAWALIGN_EINVAL then). */
+ * devices or library versions are ignored (returns RAWALIGN_EINVAL then).
+ * Caches of version 0.6.0 load as well, without their grids unless they name
+ * the anti-diagonal kernel: those were of kernels that the sweep took the place of. */
 int rawalign_load_tuning(const char *cache_path, rawalign_opts *out);
 
 /* Per-kernel timing of the last call made with RAWALIGN_FLAG_TIMING. */

@@ -1,6 +1,7 @@
 """Host code of the library compiled for tests that need no GPU."""
 import ctypes
 import os
+import shutil
 import subprocess
 import tempfile
 
@@ -10,13 +11,19 @@ CSRC = os.path.join(ROOT, "paper_2310_05037_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
+_built = {}
+
+
 def compile_host(*sources):
-    """A shared library of C++ sources (paths from this folder, or library
-    sources by name), loaded."""
-    paths = [s if os.path.exists(s) else os.path.join(CSRC, s) for s in (os.path.join(HERE, s) if os.path.exists(
-        os.path.join(HERE, s)) else s for s in sources)]
-    out = os.path.join(tempfile.mkdtemp(prefix="rawalign_host_"), "host.so")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-ffp-contract=off", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
-                    "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "include"), "-I", CSRC, *paths,
-                    "-o", out], check=True)
-    return ctypes.CDLL(out)
+    """A shared library of C++ sources (of this folder, or library sources by
+    name), compiled once and loaded anew each time: no state of earlier loads."""
+    if sources not in _built:
+        paths = [p if os.path.exists(p) else os.path.join(CSRC, s) for s in sources for p in [os.path.join(HERE, s)]]
+        out = os.path.join(tempfile.mkdtemp(prefix="rawalign_host_"), "host.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-ffp-contract=off", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
+                        "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "include"), "-I", CSRC, *paths,
+                        "-o", out], check=True)
+        _built[sources] = out
+    copy = os.path.join(tempfile.mkdtemp(prefix="rawalign_host_"), "host.so")
+    shutil.copy(_built[sources], copy)
+    return ctypes.CDLL(copy)

@@ -62,6 +62,16 @@ class Abi:
         return self._rc(self.so.rawalign_map_bnb(*self._pairs(n, q, r), I64(n), P, P, P, I64(reads), d(0.4), d(20.0), max_query, 512, P,
                                                  I64(r), P, P, P, P, P, P, VP(self.stream), self._o(opts)))
 
+    def autotune(self, n, q, r, cache=None):
+        best = Opts()
+        assert self.so.rawalign_autotune(*self._pairs(n, q, r), I64(n), P, P, VP(self.stream),
+                                         None if cache is None else cache.encode(), ctypes.byref(best)) == 0
+        return best.as_dict()
+
+    def load_tuning(self, path):
+        o = Opts()
+        return self._rc(self.so.rawalign_load_tuning(path.encode(), ctypes.byref(o))), o.as_dict()
+
     def capture(self, on):
         self.so.mock_capture(int(on))
 
