@@ -18,7 +18,7 @@ struct PlanArgs {
     const int32_t *band;   // banded planning (band half-width per pair), else null
     int paths;             // planning of the direction pass (path), whose intervals are the regions
     PathArgs path;
-    int few;               // workgroups of the sweep for many long pairs (see plan_waves)
+    int few;               // workgroups of the sweep for many long pairs (see few_waves)
     int chain_route;       // the list whose counters the chained queue's items have
 };
 
@@ -334,18 +334,12 @@ RA_DEV float plan_lim_of_grid(const PlanArgs &pa) {
     return plan_lim(pa, block_sum(threadIdx.x < gridDim.x ? pa.sw.partial[threadIdx.x] : 0.0));
 }
 
-// Workgroups of the sweep that take items (streaming calls: all).  With four pairs or more for each and
-// a million cells a pair, 16 per CU: the sweep is bound by issue then, which
-// four waves per SIMD reach as five do, and the clock stays higher (100,000
-// uneven pairs 50.7 ms against 53.3).  Fewer pairs need the fifth to hide the
-// others' waits (10,000 pairs with starts 10.5 ms against 11.1, 1,024 long
-// regions 14.7 against 15.2), shorter ones to hide their starts and ends (20,785
-// pairs of 180 events 184 us against 197).
+// The sweep's workgroups and, for the trace of paths, the share that decides
+// which pairs are cut.
 RA_DEV void plan_waves(const PlanArgs &pa, float lim) {
     const double cells = (double)lim / (double)pa.lim_scale;
-    const bool many = pa.few > 0 && !pa.extend && pa.n_pairs >= 4 * (int64_t)pa.few && cells >= (double)(1 << 20) * (double)pa.n_pairs;
-    pa.sw.n_items[2] = many ? pa.few : 0x7fffffff;
-    pa.sw.n_items[3] = __builtin_bit_cast(int, lim);   // (the trace of paths asks which were cut)
+    pa.sw.n_items[2] = !pa.extend && few_waves(pa.n_pairs, cells, pa.few) ? pa.few : 0x7fffffff;
+    pa.sw.n_items[3] = __builtin_bit_cast(int, lim);
 }
 
 // Each workgroup counts its pairs per (route, bucket) in LDS and adds the

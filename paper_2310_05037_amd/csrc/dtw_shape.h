@@ -42,6 +42,22 @@ RA_HOST_DEV inline int64_t most_items(int64_t n, int64_t m) {
     const float most = cols / (64.0f * fmaxf((float)kSweepMinC, sqrtf(26.0f * cols / rows)));
     return (int64_t)fmaxf(most, cols / (float)kSweepStripe) + 2;   // rounded up, and what rounding may add
 }
+// Many long pairs, twelve for each of `few` workgroups (16 per CU) and a million
+// cells a pair: those take all items, and the fifth wave of each SIMD is left out.
+// The sweep is bound by issue then, which four waves reach as five do, and the
+// clock stays higher.  Uneven pairs, time with 16 per CU over time with 20, on
+// 4,096 workgroups:
+//     pairs                8,192  16,384  24,576  32,768  49,152  65,536  98,304
+//     0.4 M cells a pair    0.99    1.02    0.97    0.99    1.01    1.02    1.03
+//     1.7 M                 1.01    1.02    1.00    0.97    0.96    0.97    1.00
+//     3.4 M                 1.02    1.03    1.04    1.02    0.97    0.96    0.98
+//     6.8 M                 1.05    1.03    0.99    1.06    1.00    0.98
+// (100,000 pairs of 9.2 M: 50.7 ms against 53.3).  Fewer pairs need the fifth wave
+// to hide the others' waits, shorter ones to hide their starts and ends.
+RA_HOST_DEV inline bool few_waves(int64_t n_pairs, double cells, int few) {
+    return few > 0 && n_pairs >= 12 * (int64_t)few && cells >= (double)(1 << 20) * (double)n_pairs;
+}
+
 static_assert(kEdgeCap + 3 <= kSlotFloats, "an edge column fits its slot");
 
 }  // namespace ra

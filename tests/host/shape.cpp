@@ -5,6 +5,7 @@ extern "C" {
 
 void sweep_shape(int n, int m, float lim, int *out) { ra::sweep_shape(n, m, lim, out[0], out[1], out[2]); }
 
+int few_waves(long long pairs, double cells, int few) { return ra::few_waves(pairs, cells, few); }
 long long most_items(long long n, long long m) { return ra::most_items(n, m); }
 
 int limit(int which) {

@@ -65,3 +65,16 @@ def test_large_calls_take_no_more_than_documented(_bytes):
     reference above the longest region."""
     for n, q, r in ((100000, 10 ** 8, 10 ** 8), (10 ** 6, 10 ** 6, 10 ** 8), (10 ** 6, 10 ** 6, 2000)):
         assert _bytes("batch", n, q, r) <= 900 * MB + n * (34 * 8 + 2 * 16) + 2 * MB
+
+
+def test_waves_of_large_batches(S):
+    """Where 16 waves per CU were measured to be faster than 20, they are taken;
+    where they were slower by 2 % or more, not (pairs, million cells a pair)."""
+    S.few_waves.argtypes = [ctypes.c_longlong, ctypes.c_double, ctypes.c_int]
+    few = lambda pairs, m: bool(S.few_waves(pairs, pairs * m * 1e6, 4096))
+    for pairs, m in ((49152, 1.7), (49152, 3.4), (65536, 1.7), (65536, 3.4), (65536, 6.8), (98304, 3.4), (100000, 9.2)):
+        assert few(pairs, m), (pairs, m)
+    for pairs, m in ((8192, 3.4), (8192, 6.8), (16384, 1.7), (16384, 3.4), (16384, 6.8), (24576, 3.4), (32768, 3.4), (32768, 6.8),
+                     (65536, 0.4), (98304, 0.4), (98304, 0.2), (49152, 0.2)):
+        assert not few(pairs, m), (pairs, m)
+    assert not S.few_waves(10 ** 6, 1e13, 0)
