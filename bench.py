@@ -143,7 +143,7 @@ def cpu_baseline(b, seconds: float, gpu_score=None, gpu_end=None):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_uneven_batch_traffic.txt")
-KERNEL_SOURCES = ["dtw_chain.h", "dtw_device.h", "dtw_rows.h", "dtw_sweep.hip", "internal.h"]
+KERNEL_SOURCES = ["dtw_chain.h", "dtw_device.h", "dtw_rows.h", "dtw_shape.h", "dtw_sweep.hip", "internal.h"]
 
 
 def kernel_source_hash() -> str:
@@ -232,25 +232,19 @@ def valu_rate(iters: int = 20000):
     return out
 
 
-def serving_leg(n_reads: int, rate: float, streams: int = 3, slots: int = 3, cap_frac: float = 0.5,
-                pipe_waves: int = 8, single_max: int = 2048):
+def serving_leg(n_reads: int, rate: float, slots: int = 3, cap_frac: float = 0.5):
     """Read Until serving at a fixed arrival rate, in real time: 400-event
     chunks one second apart, up to 10 chunks and 1-50 candidates per read,
     30% of the reads off target (decoy candidates only: they never map and
     stream every chunk), the decision's match bonus set for this data's noise
     floor (workloads.SYNTHETIC_B_MATCH), resident rows in an 8 GiB arena,
-    three ticks in flight, each a captured graph (`pipe_waves`, `single_max`
-    and `streams` change nothing in the
-    stripe sweep).  A short time-compressed run first warms up the graphs and
-    caches.  The same reads then run again with an
-    arena cap of `cap_frac` of the first run's peak: admission waits
+    three ticks in flight, each a captured graph.  A short time-compressed run
+    first warms up the graphs and caches.  The same reads then run again with
+    an arena cap of `cap_frac` of the first run's peak: admission waits
     (back-pressure), the cap holds, and every read's per-chunk results must
     equal the first run's."""
     from paper_2310_05037_amd import lib, serve, workloads
-    kw = dict(streams=streams, single_max=single_max)
-    if pipe_waves:
-        kw.update(long_kernel=lib.LONG_PIPELINE, pipe_waves=pipe_waves)
-    opts = lib.make_opts(**kw)
+    opts = lib.make_opts()
     bm = workloads.SYNTHETIC_B_MATCH
     warm = workloads.serving_workload(300, rate=rate, seed_index=103)
     serve.serve(warm, arena_bytes=1 << 30, time_scale=0.05, timeout=120, opts=opts, slots=slots, b_match=bm)
@@ -263,7 +257,7 @@ def serving_leg(n_reads: int, rate: float, streams: int = 3, slots: int = 3, cap
     out = {k: st[k] for k in keep if k in st}
     off = sum(1 for rd in wl.reads if rd.true_cand < 0)
     out.update({"rate_reads_per_s": rate, "chunk_events": wl.chunk, "chunk_period_s": wl.period,
-                "streams": streams, "slots": slots, "opts": {k: v for k, v in kw.items()},
+                "slots": slots,
                 "off_target_reads": off, "b_match": bm,
                 "threshold": eng.threshold,
                 "latency": "decision on host minus the moment the chunk was available"})
@@ -725,12 +719,6 @@ def main():
     ap.add_argument("--serving-reads", type=int, default=20000, help="reads in the serving leg (0: skip it)")
     ap.add_argument("--serving-rate", type=float, default=2000.0)
     ap.add_argument("--serving-slots", type=int, default=3, help="serving ticks in flight")
-    ap.add_argument("--serving-streams", type=int, default=3, choices=(1, 3),
-                    help="library streams for the serving extension (3: the three route kernels concurrently)")
-    ap.add_argument("--serving-pipe-waves", type=int, default=8, choices=(0, 2, 4, 8),
-                    help="waves sharing each long region in the serving extension (0: one wave per pair)")
-    ap.add_argument("--serving-single-max", type=int, default=2048, choices=(2048, 4096),
-                    help="widest region swept as one stripe in the serving extension")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MIB",
                     help="only run a copy kernel of this size (counter calibration)")
     ap.add_argument("--valu-rate", action="store_true",
@@ -917,8 +905,7 @@ def main():
     torch.cuda.empty_cache()
     if args.serving_reads > 0:
         note("serving")
-        out["serving"] = serving_leg(args.serving_reads, args.serving_rate, args.serving_streams, args.serving_slots,
-                                     pipe_waves=args.serving_pipe_waves, single_max=args.serving_single_max)
+        out["serving"] = serving_leg(args.serving_reads, args.serving_rate, args.serving_slots)
         checks["serving_capped_results_equal"] = out["serving"]["capped"]["results_equal_uncapped"]
     if not args.no_cpu:
         note("cpu baseline")

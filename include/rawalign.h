@@ -126,17 +126,16 @@ int rawalign_opts_default(rawalign_opts *opts);
  * pairs can have with q_size events and r_size levels, 43 MB for ten candidates
  * of a read of 1,500 events in a large reference, and 0.9 GB at most.  Work
  * items: 8 bytes each, up to 34 a pair with a long reference (0.27 GB for a
- * million pairs).  Calls on one stream are ordered by
- * the stream; calls on different streams use different scratch.  Growing the
- * scratch calls hipMalloc, so a call that may be captured into a HIP graph
- * must follow an uncaptured call of at least the same n_pairs on that stream;
- * captured before the sweep's own scratch is there, and where there is no room
- * for it, a call takes the kernels of plain mode's routes in persistent queues
- * instead.  Scratch that a
- * captured call used is kept when a later call on the stream outgrows it, so
- * the graph stays valid (at most as much again as is in use).  A sweep whose waves
- * wait for each other longer than 5 s (a GPU that does not run them) ends with
- * NaN and end RAWALIGN_END_GIVEN_UP for the pairs it cut.
+ * million pairs).  Calls on one stream are ordered by the stream; calls on
+ * different streams use different scratch.  Growing the scratch calls
+ * hipMalloc, so a call that may be captured into a HIP graph must follow an
+ * uncaptured call of at least the same n_pairs on that stream; captured before
+ * the sweep's own scratch is there, and where there is no room for it, a call
+ * takes the kernels of plain mode's routes in persistent queues instead.
+ * Scratch that a captured call used is kept when a later call on the stream
+ * outgrows it, so the graph stays valid (at most as much again as is in use).
+ * A sweep whose waves wait for each other longer than 5 s (a GPU that does not
+ * run them) ends with NaN and end RAWALIGN_END_GIVEN_UP for the pairs it cut.
  */
 #define RAWALIGN_END_GIVEN_UP (-5)
 int rawalign_dtw_batch(const float *q, int64_t q_size, const int64_t *q_off, const int32_t *q_len,
@@ -297,7 +296,8 @@ int rawalign_map_bnb(const float *q, int64_t q_size, const int64_t *q_off, const
  *   pair).  Pairs without an end keep its sentinel as their start (-1
  *   degenerate, -2 invalid, -5 given up); a pair whose reverse pass was given
  *   up (see rawalign_dtw_batch) keeps its score and end and has start -5.
- *   opts: as in rawalign_dtw_batch_ex (NULL = tuned or defaults) for both passes; long_kernel must be RAWALIGN_LONG_STRIPED.
+ *   opts: as in rawalign_dtw_batch_ex (NULL = tuned or defaults) for both
+ *   passes; long_kernel must be RAWALIGN_LONG_STRIPED.
  *   Scratch: that of rawalign_dtw_batch plus 12 bytes per pair, per (device,
  *   stream).  The reverse pass sweeps sum(e + 1) * n cells.
  */
@@ -477,7 +477,7 @@ typedef struct rawalign_timing {
     float plan_ms;    /* routing / ordering kernels */
     float lo_ms;      /* regions <= 2048 levels */
     float hi_ms;      /* regions 2049..4096 levels */
-    float long_ms;    /* regions > 4096 levels */
+    float long_ms;    /* regions > 4096 levels; the stripe sweep, which takes every region */
     float total_ms;   /* first to last event of the call */
 } rawalign_timing;
 int rawalign_last_timing(rawalign_timing *out);

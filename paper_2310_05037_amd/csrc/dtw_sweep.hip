@@ -9,7 +9,8 @@
 // wave_shr:1 moves per step; lane 0 gets them from a 64-row block in LDS, one
 // broadcast ds_read_b128 per step, read a step ahead.  Lane 63's last column
 // goes to LDS and leaves the wave as one coalesced 256-byte store per block.
-// A block costs the wave a few dozen instructions; a step costs 6 C + 5.
+// A block costs the wave about 110 instructions; a step costs 6 C + 12 vector
+// instructions and about ten others.
 //
 // A work item is one stripe of a long pair or one whole short pair.  The
 // planner lists the stripes of a pair one after another, pairs longest first,
@@ -23,8 +24,8 @@
 // batch takes all of its pair's stripes, edges through the wave's own column.
 //
 // What bounds it: instruction issue.  3.5 vector instructions per cell, a SIMD
-// issuing one in 2.2 cycles at most: 50.9 ms for 100,000 uneven pairs (0.96 T
-// cells, 18.8 T cells/s; 55 before), memory far from busy.  Few or short pairs
+// issuing one in 2.2 cycles at most: 50.3 to 52.5 ms for 100,000 uneven pairs
+// (0.96 T cells, 18.2 to 19.0 T cells/s; 55 before), memory far from busy.  Few or short pairs
 // wait for one wave's chain of dependent instructions instead.
 #include "dtw_chain.h"
 #include "dtw_rows.h"

@@ -29,9 +29,9 @@ constexpr int kSingleLoMaxRegion = 2048;               // 64 lanes x 32 columns
 constexpr int kMaxStripes = 16;
 constexpr int kMaxRegion = kMaxStripes * kShortMaxRegion;   // 65536
 // Columns per lane come in steps (C = step * h).  Single-stripe kernels use
-// steps of 2 (32 column counts per kernel).  The multi-stripe and
-// early-termination kernels use steps of 1 by default, which halves the
-// padding columns past the end of a region; the two-chain sweep needs 2.
+// steps of 2 (32 column counts per kernel).  The multi-stripe kernel uses steps
+// of 1 by default, which halves the padding columns past the end of a region;
+// the two-chain sweep needs 2.
 constexpr int kSingleColStep = 2;
 #ifndef RA_MULTI_COL_STEP
 #define RA_MULTI_COL_STEP 1
