@@ -1,4 +1,5 @@
 """Host code of the library compiled for tests that need no GPU."""
+import atexit
 import ctypes
 import os
 import shutil
@@ -14,16 +15,22 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 _built = {}
 
 
+def _folder():
+    path = tempfile.mkdtemp(prefix="rawalign_host_")
+    atexit.register(shutil.rmtree, path, ignore_errors=True)
+    return path
+
+
 def compile_host(*sources):
     """A shared library of C++ sources (of this folder, or library sources by
     name), compiled once and loaded anew each time: no state of earlier loads."""
     if sources not in _built:
         paths = [p if os.path.exists(p) else os.path.join(CSRC, s) for s in sources for p in [os.path.join(HERE, s)]]
-        out = os.path.join(tempfile.mkdtemp(prefix="rawalign_host_"), "host.so")
+        out = os.path.join(_folder(), "host.so")
         subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-ffp-contract=off", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
                         "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "include"), "-I", CSRC, *paths,
                         "-o", out], check=True)
         _built[sources] = out
-    copy = os.path.join(tempfile.mkdtemp(prefix="rawalign_host_"), "host.so")
+    copy = os.path.join(_folder(), "host.so")
     shutil.copy(_built[sources], copy)
     return ctypes.CDLL(copy)
